@@ -154,6 +154,10 @@ def _bind_eval(L) -> None:
     L.bn_stream_pattern.restype = ctypes.c_int
     L.bn_alu_probe.argtypes = [vp, ctypes.c_uint32, ctypes.c_uint32, f32, vp]
     L.bn_alu_probe.restype = ctypes.c_int
+    L.bn_cosine_loss.argtypes = [vp, vp, vp, vp, i64, vp, vp, vp, vp, vp]
+    L.bn_cosine_loss.restype = ctypes.c_int
+    L.bn_cosine_loss_vjp.argtypes = [vp, vp, i64, vp, vp, vp, vp]
+    L.bn_cosine_loss_vjp.restype = ctypes.c_int
 
 
 def _bind_batch(L) -> None:
@@ -676,10 +680,109 @@ def normals_with_grad_stack(depth, intrinsics, alpha: int = 2, mode="rel", tau: 
     return _StackFunction.apply(depth, key, int(alpha), mode, float(tau))
 
 
+COSINE_TILE = 2048               # BN_COSINE_TILE
+COSINE_MAX_PIXELS = 1 << 30      # BN_COSINE_MAX_PIXELS
+
+
+def _eager() -> bool:
+    """No transform, tracer or mode is active that would have to see the
+    tensor operations of a step (vmap, forward-mode, tracing, compilation,
+    function or dispatch modes)."""
+    import torch
+    from torch.autograd import forward_ad
+    return (torch._C._functorch.peek_interpreter_stack() is None
+            and forward_ad._current_level < 0
+            and torch._C._len_torch_dispatch_stack() == 0
+            and torch._C._len_torch_function_stack() == 0
+            and not torch.jit.is_tracing() and not torch.compiler.is_compiling())
+
+
+def _dense(t, dtype, shape, device) -> bool:
+    import torch
+    # (a batched tensor of autograd's own vmap has no storage)
+    return (type(t) is torch.Tensor and torch._C._has_storage(t) and t.dtype == dtype
+            and t.shape == shape and t.device == device and t.is_contiguous())
+
+
+def _cosine_function():
+    import torch
+
+    class CosineLoss(torch.autograd.Function):
+        """The loss in one pass (and a small sum), its gradient in another.
+        The pixels that took part are kept as their own map, so that a mask
+        buffer written again before the backward pass changes nothing."""
+
+        @staticmethod
+        def forward(ctx, normals, target, mask, target_mask):
+            dev, px = normals.device, mask.numel()
+            loss = torch.empty((), dtype=torch.float32, device=dev)
+            count = torch.empty((), dtype=torch.float32, device=dev)
+            ws = torch.empty(2 * (-(-px // COSINE_TILE)), dtype=torch.float64, device=dev)
+            used = torch.empty(mask.shape, dtype=torch.uint8, device=dev) \
+                if ctx.needs_input_grad[0] else None
+            rc = lib().bn_cosine_loss(
+                normals.data_ptr(), target.data_ptr(), mask.data_ptr(), target_mask.data_ptr(), px,
+                used.data_ptr() if used is not None else None, ws.data_ptr(), loss.data_ptr(),
+                count.data_ptr(), _stream_handle(None))
+            if rc != BN_OK:
+                raise BnError(rc, "bn_cosine_loss")
+            ctx.save_for_backward(target, used, count)
+            return loss
+
+        @staticmethod
+        def backward(ctx, grad):
+            target, used, count = ctx.saved_tensors
+            dev = target.device
+            if not (not torch.is_grad_enabled() and _eager()
+                    and _dense(grad, torch.float32, torch.Size(()), dev)
+                    and _dense(target, torch.float32, used.shape + (3,), dev)
+                    and _dense(used, torch.uint8, used.shape, dev)
+                    and _dense(count, torch.float32, torch.Size(()), dev)
+                    and dev.index == torch.cuda.current_device()):
+                # as tensor operations: a second derivative, a transform
+                scale = -(grad / count)
+                w = torch.where(used != 0, scale, torch.zeros_like(scale))
+                return w.unsqueeze(-1) * target, None, None, None
+            gn = torch.empty_like(target)
+            rc = lib().bn_cosine_loss_vjp(target.data_ptr(), used.data_ptr(), used.numel(),
+                                          grad.data_ptr(), count.data_ptr(), gn.data_ptr(),
+                                          _stream_handle(None))
+            if rc != BN_OK:
+                raise BnError(rc, "bn_cosine_loss_vjp")
+            return gn, None, None, None
+
+    return CosineLoss
+
+
+_CosineLoss = None
+
+
+def _cosine_fused(normals, target, mask, target_mask) -> bool:
+    """The arguments that the library's kernels take: dense binary32 maps
+    [..., 3] and dense uint8 masks [...] on the current GPU, nothing asking
+    for a gradient but the normals.  Everything else goes through tensor
+    operations."""
+    import torch
+    if not (type(normals) is torch.Tensor and normals.is_cuda and normals.dim() >= 2):
+        return False
+    dev, shape = normals.device, normals.shape
+    return (shape[-1] == 3 and 0 < normals.numel() <= 3 * COSINE_MAX_PIXELS
+            and _dense(normals, torch.float32, shape, dev)
+            and _dense(target, torch.float32, shape, dev) and not target.requires_grad
+            and _dense(mask, torch.uint8, shape[:-1], dev)
+            and _dense(target_mask, torch.uint8, shape[:-1], dev)
+            and dev.index == torch.cuda.current_device() and _eager())
+
+
 def cosine_loss(normals, target, mask, target_mask):
     """mean over pixels valid in both of (1 - normals . target); any leading
     shape (one frame or a stack).  No host synchronisation."""
+    global _CosineLoss
     import torch
+    if _cosine_fused(normals, target, mask, target_mask):
+        if _CosineLoss is None:
+            _CosineLoss = _cosine_function()
+        return _CosineLoss.apply(normals, target, mask, target_mask)
     U = (mask == VALID) & (target_mask == VALID)
     cos = (normals * target).sum(-1)
     return torch.where(U, 1.0 - cos, torch.zeros_like(cos)).sum() / U.sum().clamp(min=1)

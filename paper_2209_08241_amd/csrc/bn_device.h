@@ -20,6 +20,7 @@
 namespace bn {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
 
 constexpr int kBlock = 256;  // 4 wave64 per workgroup
 

@@ -368,7 +368,6 @@ __device__ __forceinline__ FitCol fit_col(const double *c, const double *q) {
 // last R lanes read there only reaches their own windows, which are not
 // outputs).
 constexpr int kFitPlane = 64 + 2 * BN_MAX_FIT_RADIUS;
-typedef double d2 __attribute__((ext_vector_type(2)));
 struct FitLds {
     d2 v[3][kFitPlane];
 };
