@@ -147,9 +147,11 @@ typedef struct bn_params {
     float tau;         /* threshold, finite and > 0 (ignored by BN_MASK_NONE) */
     uint32_t variant;  /* 0 = library's choice (the autotuner's entry for
                           the frame's size class, else vector tiles where the
-                          method and layout allow them, except four-pair
-                          frames of at most 2^19 pixels, which take the
-                          scalar tiles); else a kernel variant id
+                          method and layout allow them, except frames of at
+                          most 2^19 pixels (multi-scale: 3 * 2^17), which
+                          take the scalar tiles; where no vector tiles serve,
+                          frames above 2^20 pixels take tiles of four pixels
+                          per thread for any layout); else a kernel variant id
                           (bn_variant_count / bn_variant_name), for tests and
                           tuning: every variant writes identical output */
     int32_t method;    /* BN_METHOD_*; 0 = the paper's four-pair estimator */
@@ -267,7 +269,8 @@ int bn_normals_vjp(const float *depth, int32_t height, int32_t width, int64_t de
  *   grad_normals [n][height][width][3];  grad_depth [n][height][width] out
  * 1 <= n <= BN_MAX_STACK (n = 0, height 0 or width 0: nothing to do).
  * params->variant: 0 (vector tiles when the layout allows them, which
- * needs depth_frame_stride % 4 == 0 besides the single-frame rules), 1
+ * needs depth_frame_stride % 4 == 0 besides the single-frame rules, else
+ * tiles of four pixels per thread for any layout), 1
  * ("scalar") or 2 ("vec4") for the forward; 0 for the adjoint.
  * Errors as for the single-frame calls; BN_ERR_UNSUPPORTED for n >
  * BN_MAX_STACK.  Nothing is allocated; the arguments travel in the launch.

@@ -207,12 +207,15 @@ def default_variant(height: int, width: int, method="four_pair", alpha: int = 2,
                     scales: int = 0) -> int:
     """The variant the library takes with no autotuning entry, for dense
     frames of this size (vector tiles when the method and the layout allow
-    them, except four-pair frames of at most 2^19 pixels: scalar tiles)."""
+    them, except frames of at most 2^19 pixels, 3 * 2^17 in multi-scale: scalar
+    tiles).  1 also where no vector tiles serve, though larger frames then
+    take tiles of four pixels per thread, which are no variant of their own."""
     me = METHODS[method] if isinstance(method, str) else int(method)
     vec_method = me != METHODS["multiscale"] or alpha * max(scales, 1) <= 16
     if not (vec_method and width % 4 == 0):
         return 1
-    return 1 if (me == METHODS["four_pair"] and height * width <= (1 << 19)) else 2
+    small = 3 << 17 if me == METHODS["multiscale"] else 1 << 19
+    return 1 if height * width <= small else 2
 
 
 def variants() -> Sequence[Tuple[int, str]]:

@@ -41,7 +41,7 @@ struct BatchFrame {
     FrameArgs a;
     uint32_t tile_begin;  // first tile in the batch-wide tile sequence
     uint32_t ntiles;
-    uint32_t vec;         // 1: vector tiles, 0: scalar tiles
+    uint32_t kind;        // kTile*
     uint32_t pad;
 };
 
@@ -65,7 +65,10 @@ struct BatchHeader {
 // measured mean occupancy was 6.5 against 7.6 for the kernels of 61-67
 // registers; capped at 80 (a few spills to VGPR lanes) the 256-frame mix
 // runs 540 -> 527 us (72 and 64 spill more and are slower).
-template <int A, int M>
+// FLAT: the list holds frames that take flat tiles.  Lists without any run the
+// kernel without that body: with it, 65 to 92 VGPRs instead of 49 to 64, the
+// 128-frame mix in multi-scale took 340 instead of 332 us.
+template <int A, int M, bool FLAT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void k_batch(
     const BatchFrame *__restrict__ frames,
                                                   const uint32_t *__restrict__ tile_frame,
@@ -85,11 +88,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void k
         frame_pointers_global(f, &frames[fi].a);
         const uint32_t tb = frames[fi].tile_begin;
         const uint32_t nt = frames[fi].ntiles;
-        const bool vec = frames[fi].vec != 0;
+        const uint32_t kind = frames[fi].kind;
         const uint32_t seg_end = min(tend, tb + nt);
         for (; t < seg_end; ++t) {
             uint32_t cv = 0, cb = 0;
-            run_tile<A, M>(f, vec, t - tb, lds, cv, cb);
+            run_tile<A, M, FLAT>(f, kind, t - tb, lds, cv, cb);
             if (f.stats && lane == 0) wave_counts[4 * (int64_t)t + wave] = cv | (cb << 16);
         }
         // done (always so in the flat shape) before looking at the next
@@ -160,7 +163,7 @@ constexpr int kSmallFrames = BN_SMALL_BATCH;
 struct SmallBatch {
     uint32_t nframes;
     uint32_t ntiles;
-    uint32_t vec_bits;                       // bit k: frame k takes vector tiles
+    uint32_t kinds;                          // 2 bits per frame: kTile*
     uint32_t pad;
     uint32_t tile_begin[kSmallFrames];       // unused entries: UINT32_MAX
     uint32_t tile_count[kSmallFrames];
@@ -181,8 +184,13 @@ __global__ __launch_bounds__(kBlock) void k_batch_small(const SmallBatch s) {
     const FrameArgs f = s.f[k];
     const uint32_t tile = b - s.tile_begin[k];
     const uint32_t nparts = s.tile_count[k];
-    if ((s.vec_bits >> k) & 1u) {
+    const uint32_t kind = (s.kinds >> (2u * k)) & 3u;
+    if (kind == kTileVec4) {
         vec4_tile_counted<A, M>(f, tile, tile, nparts, lds);
+        return;
+    }
+    if (kind == kTileFlat) {
+        flat_tile_counted<M>(f, tile, tile, nparts, lds);
         return;
     }
     scalar_tile_counted<A, M>(f, tile, tile, nparts, lds);
@@ -216,27 +224,28 @@ static SmallKernelFn small_kernel(int method, int alpha, int scales) {
     return nullptr;
 }
 
-template <int M>
+template <int M, bool FLAT>
 static BatchKernelFn batch_kernel_m(int alpha) {
     switch (alpha) {
-        case 1: return k_batch<1, M>;
-        case 2: return k_batch<2, M>;
-        case 3: return k_batch<3, M>;
-        case 4: return k_batch<4, M>;
-        case 5: return k_batch<5, M>;
-        case 6: return k_batch<6, M>;
-        case 7: return k_batch<7, M>;
-        case 8: return k_batch<8, M>;
+        case 1: return k_batch<1, M, FLAT>;
+        case 2: return k_batch<2, M, FLAT>;
+        case 3: return k_batch<3, M, FLAT>;
+        case 4: return k_batch<4, M, FLAT>;
+        case 5: return k_batch<5, M, FLAT>;
+        case 6: return k_batch<6, M, FLAT>;
+        case 7: return k_batch<7, M, FLAT>;
+        case 8: return k_batch<8, M, FLAT>;
     }
     return nullptr;
 }
 
+template <bool FLAT>
 static BatchKernelFn batch_kernel(int method, int alpha, int scales) {
     method = kernel_method(method, alpha, scales);
-    if (method == kFourPair) return batch_kernel_m<kFourPair>(alpha);
-    if (method == kPairRemoval) return batch_kernel_m<kPairRemoval>(alpha);
-    if (method == kMultiScale) return batch_kernel_m<kMultiScale>(alpha);
-    if (method == kMultiScaleLong) return batch_kernel_m<kMultiScaleLong>(alpha);
+    if (method == kFourPair) return batch_kernel_m<kFourPair, FLAT>(alpha);
+    if (method == kPairRemoval) return batch_kernel_m<kPairRemoval, FLAT>(alpha);
+    if (method == kMultiScale) return batch_kernel_m<kMultiScale, FLAT>(alpha);
+    if (method == kMultiScaleLong) return batch_kernel_m<kMultiScaleLong, FLAT>(alpha);
     return nullptr;
 }
 
@@ -261,14 +270,19 @@ struct bn_batch_plan {
     hipEvent_t staged[2] = {nullptr, nullptr};
     int next = 0;                  // staging copy the next update writes
     uint32_t *dcounts = nullptr;   // 4 wavefront counts per tile (tile_capacity tiles)
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    hipGraphNode_t node = nullptr;         // the tile kernel
-    hipGraphNode_t count_node = nullptr;   // the per-frame count sums
-    BatchKernelFn fn = nullptr;
+    // one graph per tile kernel, made when a list first needs it: [0] for lists
+    // without flat tiles, [1] with
+    struct TableGraph {
+        hipGraph_t graph = nullptr;
+        hipGraphExec_t exec = nullptr;
+        hipGraphNode_t node = nullptr;         // the tile kernel
+        hipGraphNode_t count_node = nullptr;   // the per-frame count sums
+        bool stale = true;                     // node parameters behind the frame list
+    } graphs[2];
+    BatchKernelFn fns[2] = {nullptr, nullptr};
+    int has_flat = 0;                      // the current list's kernel and graph
     BatchHeader hdr{};                     // current header (kernel arguments)
-    bool graph_stale = false;              // node parameters behind the frame list
-    uint64_t total_tiles = 0;
+    uint64_t total_units = 0;      // count_frames' units
     uint64_t total_pixels = 0;
     // small lists (at most kSmallFrames frames): descriptors in the kernel
     // arguments, counts reduced on `work`, one kernel (graph sgraph/sexec)
@@ -297,15 +311,26 @@ size_t buffer_bytes(int32_t capacity, uint64_t tile_capacity) {
     return table_offset(capacity) + sizeof(uint32_t) * (size_t)tile_capacity;
 }
 
-// Vector tiles for this frame under these parameters?
-bool frame_vec(const bn_frame &s, const bn_params *p) {
-    return method_has_vec4(p) && vec4_layout(s.depth, s.width, s.depth_stride, s.normals, s.mask);
+// The tiles of this frame under these parameters.  (A list fills the chip
+// together, so the flat tiles serve its small frames too.)
+uint32_t frame_kind(const bn_frame &s, const bn_params *p) {
+    if (method_has_vec4(p) && vec4_layout(s.depth, s.width, s.depth_stride, s.normals, s.mask))
+        return kTileVec4;
+    return flat_layout(s.width, s.normals, s.mask) ? kTileFlat : kTileScalar;
 }
 
-// Validate the frames; total tiles and pixels.
+// fill_frame_args' pixels per work item.
+int kind_items(uint32_t kind) {
+    return kind == kTileVec4 ? 4 : kind == kTileFlat ? kFlatItems : 1;
+}
+
+// Validate the frames; total tiles and pixels.  `units`: the list's size as
+// bn_batch_plan_info reports it and its limits count it, in tiles of 256 work
+// items of 4 pixels (vector layouts) or 1 pixel (any other, though flat tiles
+// take four pixels per work item there too).
 int count_frames(const bn_frame *frames, int32_t n, const bn_params *p, uint64_t *tiles,
-                 uint64_t *pixels) {
-    uint64_t t = 0, px = 0;
+                 uint64_t *units, uint64_t *pixels) {
+    uint64_t t = 0, u = 0, px = 0;
     for (int32_t k = 0; k < n; ++k) {
         const bn_frame &s = frames[k];
         int rc = check_frame_args(s.depth, s.height, s.width, s.depth_stride, s.fx, s.fy, s.cx,
@@ -313,14 +338,18 @@ int count_frames(const bn_frame *frames, int32_t n, const bn_params *p, uint64_t
         if (rc == BN_OK) rc = check_stats_arg(s.stats);
         if (rc != BN_OK) return rc;
         if (s.height > 0 && s.width > 0) {
-            const bool vec = frame_vec(s, p);
-            const uint64_t items = (uint64_t)s.height * (uint64_t)(vec ? s.width / 4 : s.width);
-            t += (items + kBlock - 1) / kBlock;
+            const uint32_t kind = frame_kind(s, p);
+            FrameArgs f;
+            fill_frame_args(f, s.depth, s.height, s.width, s.depth_stride, s.fx, s.fy, s.cx, s.cy,
+                            p, s.normals, s.mask, s.stats, kind_items(kind));
+            t += ((uint64_t)f.nitems + kBlock - 1) / kBlock;
+            u += ((uint64_t)(kind == kTileVec4 ? f.nitems : f.npix) + kBlock - 1) / kBlock;
             px += (uint64_t)s.height * (uint64_t)s.width;
         }
     }
-    if (t > 0x7fffffffull) return BN_ERR_UNSUPPORTED;
+    if (u > 0x7fffffffull) return BN_ERR_UNSUPPORTED;
     *tiles = t;
+    *units = u;
     *pixels = px;
     return BN_OK;
 }
@@ -336,23 +365,31 @@ uint32_t grid_for(uint64_t tiles, int cus, int32_t shape) {
     return (uint32_t)cus * (uint32_t)shape;
 }
 
+// Parts of at most 4096 tiles, so that they stay below 2^22 pixels.
+bool chunk_ok(uint64_t units, int cus, int32_t shape) {
+    const uint64_t grid = grid_for(units, cus, shape);
+    return units == 0 || (units + grid - 1) / grid <= 4096;
+}
+
 // Host image of the descriptors of `frames` (already validated) in `base`.
 int build_table(const bn_frame *frames, int32_t n, const bn_params *p, int32_t capacity,
-                uint32_t grid, WorkArea *work, uint32_t *count_chunks, void *base) {
+                uint32_t grid, WorkArea *work, uint32_t *count_chunks, int *has_flat,
+                void *base) {
     auto *hdr = static_cast<BatchHeader *>(base);
     auto *fr = reinterpret_cast<BatchFrame *>(hdr + 1);
     auto *tf = reinterpret_cast<uint32_t *>(static_cast<char *>(base) + table_offset(capacity));
     uint64_t tiles = 0;
     *count_chunks = 1;
+    *has_flat = 0;
     for (int32_t k = 0; k < n; ++k) {
         const bn_frame &s = frames[k];
-        const bool vec = frame_vec(s, p);
+        const uint32_t kind = frame_kind(s, p);
         BatchFrame b;
         std::memset(&b, 0, sizeof(b));
         uint64_t nt = 0;
         if (s.height > 0 && s.width > 0) {
             fill_frame_args(b.a, s.depth, s.height, s.width, s.depth_stride, s.fx, s.fy, s.cx,
-                            s.cy, p, s.normals, s.mask, s.stats, vec ? 4 : 1);
+                            s.cy, p, s.normals, s.mask, s.stats, kind_items(kind));
             b.a.work = work + k;
             nt = ((uint64_t)b.a.nitems + kBlock - 1) / kBlock;
         }
@@ -360,7 +397,8 @@ int build_table(const bn_frame *frames, int32_t n, const bn_params *p, int32_t c
         if (nc > *count_chunks) *count_chunks = nc;
         b.tile_begin = (uint32_t)tiles;
         b.ntiles = (uint32_t)nt;
-        b.vec = vec ? 1u : 0u;
+        b.kind = kind;
+        if (kind == kTileFlat && nt > 0) *has_flat = 1;
         for (uint64_t t = 0; t < nt; ++t) tf[tiles + t] = (uint32_t)k;
         tiles += nt;
         fr[k] = b;
@@ -382,17 +420,17 @@ void fill_small(SmallBatch &sb, const bn_frame *frames, int32_t n, const bn_para
     for (int k = 0; k < kSmallFrames; ++k) sb.tile_begin[k] = UINT32_MAX;
     for (int32_t k = 0; k < n; ++k) {
         const bn_frame &s = frames[k];
-        const bool vec = frame_vec(s, params);
+        const uint32_t kind = frame_kind(s, params);
         uint32_t nt = 0;
         if (s.height > 0 && s.width > 0) {
             fill_frame_args(sb.f[k], s.depth, s.height, s.width, s.depth_stride, s.fx, s.fy, s.cx,
-                            s.cy, params, s.normals, s.mask, s.stats, vec ? 4 : 1);
+                            s.cy, params, s.normals, s.mask, s.stats, kind_items(kind));
             sb.f[k].work = work + k;
             nt = (sb.f[k].nitems + kBlock - 1) / kBlock;
         }
         sb.tile_begin[k] = tiles;
         sb.tile_count[k] = nt;
-        if (vec) sb.vec_bits |= 1u << k;
+        sb.kinds |= kind << (2 * k);
         tiles += nt;
     }
     sb.nframes = (uint32_t)n;
@@ -446,20 +484,22 @@ struct BatchArgs {
 // graph, or a fresh graph [tile kernel] -> [count sums] when none exists.
 int refresh_node(bn_batch_plan *pl) {
     BatchArgs a(pl);
-    hipKernelNodeParams kp = kernel_params(reinterpret_cast<void *>(pl->fn), pl->grid, a.main);
+    bn_batch_plan::TableGraph &g = pl->graphs[pl->has_flat];
+    hipKernelNodeParams kp =
+        kernel_params(reinterpret_cast<void *>(pl->fns[pl->has_flat]), pl->grid, a.main);
     hipKernelNodeParams cp = kernel_params(reinterpret_cast<void *>(k_batch_counts),
                                            a.count_grid(pl), a.counts);
-    pl->graph_stale = false;
-    if (!pl->exec) {
-        if (hipGraphCreate(&pl->graph, 0) != hipSuccess ||
-            hipGraphAddKernelNode(&pl->node, pl->graph, nullptr, 0, &kp) != hipSuccess ||
-            hipGraphAddKernelNode(&pl->count_node, pl->graph, &pl->node, 1, &cp) != hipSuccess ||
-            hipGraphInstantiate(&pl->exec, pl->graph, nullptr, nullptr, 0) != hipSuccess)
+    g.stale = false;
+    if (!g.exec) {
+        if (hipGraphCreate(&g.graph, 0) != hipSuccess ||
+            hipGraphAddKernelNode(&g.node, g.graph, nullptr, 0, &kp) != hipSuccess ||
+            hipGraphAddKernelNode(&g.count_node, g.graph, &g.node, 1, &cp) != hipSuccess ||
+            hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0) != hipSuccess)
             return BN_ERR_DEVICE;
         return BN_OK;
     }
-    if (hipGraphExecKernelNodeSetParams(pl->exec, pl->node, &kp) != hipSuccess ||
-        hipGraphExecKernelNodeSetParams(pl->exec, pl->count_node, &cp) != hipSuccess)
+    if (hipGraphExecKernelNodeSetParams(g.exec, g.node, &kp) != hipSuccess ||
+        hipGraphExecKernelNodeSetParams(g.exec, g.count_node, &cp) != hipSuccess)
         return BN_ERR_DEVICE;
     return BN_OK;
 }
@@ -495,8 +535,10 @@ void free_plan(bn_batch_plan *pl) {
             (void)hipEventDestroy(pl->staged[k]);
         }
     }
-    if (pl->exec) (void)hipGraphExecDestroy(pl->exec);
-    if (pl->graph) (void)hipGraphDestroy(pl->graph);
+    for (auto &g : pl->graphs) {
+        if (g.exec) (void)hipGraphExecDestroy(g.exec);
+        if (g.graph) (void)hipGraphDestroy(g.graph);
+    }
     if (pl->sexec) (void)hipGraphExecDestroy(pl->sexec);
     if (pl->sgraph) (void)hipGraphDestroy(pl->sgraph);
     if (pl->work) (void)hipFree(pl->work);
@@ -528,7 +570,7 @@ int refresh_small_node(bn_batch_plan *pl) {
 int upload(bn_batch_plan *pl, const bn_frame *frames, int32_t n, int k, hipStream_t stream,
            uint64_t tiles) {
     int rc = build_table(frames, n, &pl->params, pl->capacity, pl->grid, pl->work,
-                         &pl->count_chunks, pl->staging[k]);
+                         &pl->count_chunks, &pl->has_flat, pl->staging[k]);
     if (rc != BN_OK) return rc;
     pl->hdr = *static_cast<const BatchHeader *>(pl->staging[k]);
     const size_t bytes = table_offset(pl->capacity) + sizeof(uint32_t) * (size_t)tiles;
@@ -555,18 +597,20 @@ int bn_batch_plan_create(const bn_frame *frames_host, int32_t n_frames, const bn
     int rc = check_params_args(params);
     if (rc != BN_OK) return rc;
     if (params->variant != VAR_AUTO) return BN_ERR_UNSUPPORTED;
-    BatchKernelFn fn = batch_kernel(params->method, params->alpha, params->scales);
+    BatchKernelFn fn = batch_kernel<false>(params->method, params->alpha, params->scales);
+    BatchKernelFn ffn = batch_kernel<true>(params->method, params->alpha, params->scales);
     SmallKernelFn sfn = small_kernel(params->method, params->alpha, params->scales);
-    if (!fn || !sfn) return BN_ERR_UNSUPPORTED;
-    uint64_t tiles = 0, pixels = 0;
-    rc = count_frames(frames_host, n_frames, params, &tiles, &pixels);
+    if (!fn || !ffn || !sfn) return BN_ERR_UNSUPPORTED;
+    uint64_t tiles = 0, units = 0, pixels = 0;
+    rc = count_frames(frames_host, n_frames, params, &tiles, &units, &pixels);
     if (rc != BN_OK) return rc;
 
     bn_batch_plan *pl = new (std::nothrow) bn_batch_plan();
     if (!pl) return BN_ERR_OOM;
     pl->params = *params;
     pl->capacity = n_frames;
-    pl->fn = fn;
+    pl->fns[0] = fn;
+    pl->fns[1] = ffn;
     pl->small_fn = sfn;
     if (hipGetDevice(&pl->device) != hipSuccess) {
         free_plan(pl);
@@ -583,7 +627,11 @@ int bn_batch_plan_create(const bn_frame *frames_host, int32_t n_frames, const bn
     const int tuned = tuned_batch_shape(params->method, params->alpha, pixels);
     pl->shape = tuned == -1 ? kFlat : tuned;
     pl->grid = grid_for(tiles, cus, pl->shape);
-    pl->total_tiles = tiles;
+    if (!chunk_ok(units, cus, pl->shape)) {
+        free_plan(pl);
+        return BN_ERR_UNSUPPORTED;
+    }
+    pl->total_units = units;
     pl->total_pixels = pixels;
     for (int k = 0; k < 2; ++k) {
         if (hipEventCreateWithFlags(&pl->staged[k], hipEventDisableTiming) != hipSuccess) {
@@ -604,7 +652,8 @@ int bn_batch_plan_create(const bn_frame *frames_host, int32_t n_frames, const bn
     }
     rc = alloc_buffers(pl, tiles > 0 ? tiles : 1);
     if (rc == BN_OK) rc = build_table(frames_host, n_frames, params, pl->capacity, pl->grid,
-                                      pl->work, &pl->count_chunks, pl->staging[0]);
+                                      pl->work, &pl->count_chunks, &pl->has_flat,
+                                      pl->staging[0]);
     if (rc == BN_OK) pl->hdr = *static_cast<const BatchHeader *>(pl->staging[0]);
     if (rc == BN_OK &&
         hipMemcpy(pl->dbuf, pl->staging[0], pl->buf_bytes, hipMemcpyHostToDevice) != hipSuccess)
@@ -629,21 +678,21 @@ int bn_batch_plan_update(bn_batch_plan *plan, const bn_frame *frames_host, int32
     if (!plan || !frames_host || n_frames < 1) return BN_ERR_INVALID_ARG;
     if (n_frames > plan->capacity) return BN_ERR_UNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
-    uint64_t tiles = 0, pixels = 0;
-    int rc = count_frames(frames_host, n_frames, &plan->params, &tiles, &pixels);
+    uint64_t tiles = 0, units = 0, pixels = 0;
+    int rc = count_frames(frames_host, n_frames, &plan->params, &tiles, &units, &pixels);
     if (rc != BN_OK) return rc;
     if (n_frames <= kSmallFrames) {
         // descriptors in the kernel arguments: nothing to upload
         build_small(plan, frames_host, n_frames);
         plan->small_mode = true;
         plan->small_stale = true;
-        plan->total_tiles = tiles;
+        plan->total_units = units;
         plan->total_pixels = pixels;
         return BN_OK;
     }
     plan->small_mode = false;
     const uint32_t grid = grid_for(tiles, plan->cus, plan->shape);
-    if (tiles > 0 && (tiles + grid - 1) / grid > 4096) return BN_ERR_UNSUPPORTED;
+    if (!chunk_ok(units, plan->cus, plan->shape)) return BN_ERR_UNSUPPORTED;
     if (tiles > plan->tile_capacity) {
         // a larger tile table: wait for every use of the old buffers first
         if (hipStreamSynchronize(s) != hipSuccess ||
@@ -678,15 +727,15 @@ int bn_batch_plan_update(bn_batch_plan *plan, const bn_frame *frames_host, int32
     rc = upload(plan, frames_host, n_frames, k, s, tiles);
     if (rc != BN_OK) return rc;
     plan->next = 1 - k;
-    plan->total_tiles = tiles;
+    plan->total_units = units;
     plan->total_pixels = pixels;
     // new header values, grids and pointers reach the graph at its next run
-    plan->graph_stale = true;
+    for (auto &g : plan->graphs) g.stale = true;
     return BN_OK;
 }
 
 int bn_batch_run(bn_batch_plan *plan, void *stream) {
-    if (!plan || !plan->exec) return BN_ERR_INVALID_ARG;
+    if (!plan) return BN_ERR_INVALID_ARG;
     if (plan->small_mode) {
         if (plan->small.ntiles == 0) return BN_OK;  // only empty frames
         if (plan->small_stale) {
@@ -696,15 +745,16 @@ int bn_batch_run(bn_batch_plan *plan, void *stream) {
         return hipGraphLaunch(plan->sexec, (hipStream_t)stream) == hipSuccess ? BN_OK
                                                                               : BN_ERR_DEVICE;
     }
-    if (plan->graph_stale) {
+    bn_batch_plan::TableGraph &g = plan->graphs[plan->has_flat];
+    if (g.stale) {
         const int rc = refresh_node(plan);
         if (rc != BN_OK) return rc;
     }
-    return hipGraphLaunch(plan->exec, (hipStream_t)stream) == hipSuccess ? BN_OK : BN_ERR_DEVICE;
+    return hipGraphLaunch(g.exec, (hipStream_t)stream) == hipSuccess ? BN_OK : BN_ERR_DEVICE;
 }
 
 int bn_batch_launch(bn_batch_plan *plan, void *stream) {
-    if (!plan || !plan->exec) return BN_ERR_INVALID_ARG;
+    if (!plan) return BN_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (plan->small_mode) {
         if (plan->small.ntiles == 0) return BN_OK;  // only empty frames
@@ -715,7 +765,7 @@ int bn_batch_launch(bn_batch_plan *plan, void *stream) {
                    : BN_ERR_DEVICE;
     }
     BatchArgs a(plan);
-    if (hipLaunchKernel(reinterpret_cast<const void *>(plan->fn), dim3(plan->grid),
+    if (hipLaunchKernel(reinterpret_cast<const void *>(plan->fns[plan->has_flat]), dim3(plan->grid),
                         dim3(kBlock), a.main, 0, s) != hipSuccess ||
         hipLaunchKernel(reinterpret_cast<const void *>(k_batch_counts), a.count_grid(plan),
                         dim3(kBlock), a.counts, 0, s) != hipSuccess)
@@ -727,9 +777,11 @@ int bn_batch_plan_info(const bn_batch_plan *plan, int64_t *n_pixels, int64_t *n_
                        int32_t *n_workgroups) {
     if (!plan) return BN_ERR_INVALID_ARG;
     if (n_pixels) *n_pixels = (int64_t)plan->total_pixels;
-    if (n_tiles) *n_tiles = (int64_t)plan->total_tiles;
+    if (n_tiles) *n_tiles = (int64_t)plan->total_units;
     if (n_workgroups)
-        *n_workgroups = (int32_t)(plan->small_mode ? plan->small.ntiles : plan->grid);
+        *n_workgroups = (int32_t)(plan->small_mode
+                                      ? plan->total_units
+                                      : grid_for(plan->total_units, plan->cus, plan->shape));
     return BN_OK;
 }
 
@@ -739,7 +791,7 @@ static int set_grid(bn_batch_plan *plan, int32_t shape, hipStream_t stream) {
     (void)stream;
     const uint32_t grid = grid_for(plan->hdr.ntiles, plan->cus, shape);
     const uint32_t chunk = plan->hdr.ntiles ? (plan->hdr.ntiles + grid - 1) / grid : 0;
-    if (chunk > 4096) return BN_ERR_UNSUPPORTED;
+    if (!chunk_ok(plan->total_units, plan->cus, shape)) return BN_ERR_UNSUPPORTED;
     plan->shape = shape;
     plan->grid = grid;
     plan->hdr.chunk = chunk;
@@ -748,7 +800,7 @@ static int set_grid(bn_batch_plan *plan, int32_t shape, hipStream_t stream) {
 
 int bn_batch_plan_autotune(bn_batch_plan *plan, void *stream, int32_t *best_shape,
                            float *best_us) {
-    if (!plan || !plan->exec) return BN_ERR_INVALID_ARG;
+    if (!plan) return BN_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return BN_ERR_DEVICE;
@@ -782,13 +834,13 @@ int bn_batch_plan_autotune(bn_batch_plan *plan, void *stream, int32_t *best_shap
         rc = set_grid(plan, c, s);
         if (rc == BN_ERR_UNSUPPORTED) continue;
         if (rc != BN_OK) break;
-        if (hipGraphLaunch(plan->exec, s) != hipSuccess) {
+        if (hipGraphLaunch(plan->graphs[plan->has_flat].exec, s) != hipSuccess) {
             rc = BN_ERR_DEVICE;
             break;
         }
         (void)hipEventRecord(e0, s);
         const int reps = 3;
-        for (int r = 0; r < reps; ++r) (void)hipGraphLaunch(plan->exec, s);
+        for (int r = 0; r < reps; ++r) (void)hipGraphLaunch(plan->graphs[plan->has_flat].exec, s);
         (void)hipEventRecord(e1, s);
         if (hipEventSynchronize(e1) != hipSuccess) {
             rc = BN_ERR_DEVICE;
@@ -868,8 +920,8 @@ extern "C" int bn_estimate_normals_batch_noalloc(const bn_frame *frames_host, in
     if (params->variant != VAR_AUTO) return BN_ERR_UNSUPPORTED;
     SmallKernelFn fn = small_kernel(params->method, params->alpha, params->scales);
     if (!fn) return BN_ERR_UNSUPPORTED;
-    uint64_t tiles = 0, pixels = 0;
-    rc = count_frames(frames_host, n_frames, params, &tiles, &pixels);
+    uint64_t tiles = 0, units = 0, pixels = 0;
+    rc = count_frames(frames_host, n_frames, params, &tiles, &units, &pixels);
     if (rc != BN_OK) return rc;
     if (tiles == 0) return BN_OK;  // only empty frames
     WorkArea *work = nullptr;

@@ -43,16 +43,35 @@ bool method_has_vec4(const bn_params *p) {
     return p->method != BN_METHOD_MULTISCALE || p->alpha * p->scales <= kMsVecReach;
 }
 
+// Positions s before the frame's first pixel such that position 0 of the
+// normals lies on a 128-byte line (12 s = address mod 128, so s = 11 address/4
+// mod 32) and that of the codes on a 4-byte word, on a 128-byte line where it
+// can; -1 where the two arrays' alignments exclude each other.
+static int flat_shift(const float *normals, const uint8_t *mask) {
+    const uint32_t s = (11u * (uint32_t)(((uintptr_t)normals / 4u) % 32u)) % 32u;
+    if (((uintptr_t)mask - s) % 4u != 0) return -1;
+    for (uint32_t k = 0; k < 4; ++k)
+        if (((uintptr_t)mask - (s + 32u * k)) % 128u == 0) return (int)(s + 32u * k);
+    return (int)s;
+}
+
+bool flat_layout(int32_t W, const float *normals, const uint8_t *mask) {
+    return W >= 4 && flat_shift(normals, mask) >= 0;
+}
+
 // A small frame has few tiles: at 1024 pixels a tile, a 640x480 frame is
 // 1200 wavefronts, about one per SIMD, and its launch is one chain of
 // latencies; at one pixel a thread it is 4800 wavefronts whose latencies
-// overlap.  Four-pair, graph-replayed: 320x240 3.19 against 3.60-3.81 us,
-// 640x480 3.77 against 4.25-4.37 us for the vector shapes; 1280x720 the
-// same within 1.5%; 1920x1080 9.2 against 7.5 us.
+// overlap.  Graph-replayed, scalar against vector tiles.  Four-pair: 320x240
+// 3.19 / 3.60-3.81 us, 640x480 3.77 / 4.25-4.37, 1280x720 the same within
+// 1.5%, 1920x1080 9.2 / 7.5.  Pair removal: 320x240 3.8 / 4.7, 640x480 4.25 /
+// 5.2, 1280x720 6.7 / 6.6.  Multi-scale, K = 1, 3, 6: 320x240 3.5, 3.9, 4.4 /
+// 4.3, 4.6, 5.1; 640x480 4.0, 4.6, 5.2 / 4.5, 5.0, 5.7; 1280x720 (K = 3) 7.5 /
+// 5.9.
 int default_plain_variant(const bn_params *p, uint64_t pixels, bool vec_layout) {
     if (!vec_layout || !method_has_vec4(p)) return VAR_SCALAR;
-    if (p->method == BN_METHOD_FOUR_PAIR && pixels <= kSmallFrame) return VAR_SCALAR;
-    return VAR_VEC4;
+    const uint64_t small = p->method == BN_METHOD_MULTISCALE ? kSmallFrameMs : kSmallFrame;
+    return pixels <= small ? VAR_SCALAR : VAR_VEC4;
 }
 
 int check_frame_args(const float *depth, int32_t H, int32_t W, int64_t stride, float fx,
@@ -132,10 +151,13 @@ static float abs_threshold(int method, int scales, float fx, float fy, float tau
 
 static int pick_variant(const float *depth, int32_t H, int32_t W, int64_t stride,
                         const float *normals, const uint8_t *mask, const bn_params *p) {
-    const int tuned = tuned_plain_variant(p->method, p->alpha, (uint64_t)H * (uint64_t)W);
+    const uint64_t px = (uint64_t)H * (uint64_t)W;
+    const bool vec = vec4_layout(depth, W, stride, normals, mask);
+    if (!(vec && method_has_vec4(p)))
+        return px > kSmallRagged && flat_layout(W, normals, mask) ? VAR_FLAT : VAR_SCALAR;
+    const int tuned = tuned_plain_variant(p->method, p->alpha, px);
     if (tuned > 0 && method_variant_ok(p, tuned, depth, W, stride, normals, mask)) return tuned;
-    return default_plain_variant(p, (uint64_t)H * (uint64_t)W,
-                                 vec4_layout(depth, W, stride, normals, mask));
+    return default_plain_variant(p, px, vec);
 }
 
 void fill_frame_args(FrameArgs &f, const float *depth, int32_t H, int32_t W, int64_t stride,
@@ -159,9 +181,16 @@ void fill_frame_args(FrameArgs &f, const float *depth, int32_t H, int32_t W, int
     f.hconst = p->mask_mode == BN_MASK_ABS
                    ? abs_threshold(p->method, p->scales, fx, fy, p->tau, p->alpha)
                    : INFINITY;
-    f.gpr = (uint32_t)(W / px_per_item);
-    f.nitems = f.gpr * (uint32_t)H;
     f.npix = (uint32_t)H * (uint32_t)W;
+    if (px_per_item == kFlatItems) {
+        f.shift = (uint32_t)flat_shift(normals, mask);
+        f.gpr = (uint32_t)W;
+        f.nitems = (f.npix + f.shift + 3u) / 4u;
+    } else {
+        f.shift = 0;
+        f.gpr = (uint32_t)(W / px_per_item);
+        f.nitems = f.gpr * (uint32_t)H;
+    }
     f.alpha = p->alpha;
     f.scales = p->method == BN_METHOD_MULTISCALE ? p->scales : 1;
     f.overwrite = (p->flags & BN_FLAG_COUNTS_ACCUMULATE) ? 0u : 1u;
@@ -190,7 +219,7 @@ int bn_estimate_normals(const float *depth, int32_t height, int32_t width, int64
     }
     FrameArgs f;
     fill_frame_args(f, depth, height, width, depth_stride, fx, fy, cx, cy, params, normals, mask,
-                    stats, variant_info(v)->px_per_item);
+                    stats, v == VAR_FLAT ? kFlatItems : variant_info(v)->px_per_item);
     if (stats) {
         rc = stream_work_areas((hipStream_t)stream, &f.work);
         if (rc != BN_OK) return rc;

@@ -55,7 +55,11 @@ struct FrameArgs {
     int32_t scales;   // K of the multi-scale method
     uint32_t overwrite;  // 1: counts replace the stats counters, 0: added (accumulate)
     double inv_gpr;   // 1.0 / gpr
+    uint32_t shift;   // flat tiles: positions before the frame's first pixel (0..255)
 };
+
+// Kinds of tile a frame of a stack or batch takes.
+constexpr uint32_t kTileScalar = 0, kTileVec4 = 1, kTileFlat = 2;
 
 // A stack of frames of one size in one launch: the first frame's arguments,
 // the distance between frames' depth, and what differs per frame (the
@@ -71,7 +75,7 @@ struct StackArgs {
     int64_t depth_fstride;     // elements from one frame's depth to the next
     uint32_t n;                // frames
     uint32_t tiles_per_frame;  // workgroups per frame
-    uint32_t vec;              // 1: vector tiles
+    uint32_t kind;             // kTile*
     uint32_t tiles_x;          // adjoint: tiles per row
     const float *gn;           // adjoint: cotangent [n][H][W][3]
     float *gd;                 // adjoint: gradient [n][H][W]

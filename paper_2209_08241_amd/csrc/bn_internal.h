@@ -16,7 +16,10 @@ enum Variant {
     VAR_VEC4_P2 = 5,  // 2 groups of 4 pixels per thread, second tile's loads ahead
     VAR_VEC4_W128 = 6,  // 4 pixels per thread, workgroups of 128 threads
     VAR_VEC4_W64 = 7,   // 4 pixels per thread, workgroups of 64 threads
-    VAR_COUNT = 7
+    VAR_COUNT = 7,
+    // not a variant of the interface: what VAR_AUTO takes where the vector
+    // tiles don't serve and flat_layout holds
+    VAR_FLAT = 100
 };
 
 struct VariantInfo {
@@ -42,14 +45,29 @@ int stream_work_areas(hipStream_t stream, WorkArea **out);
 // True when the frame can use the 4-pixel vector tiles.
 bool vec4_layout(const float *depth, int32_t W, int64_t stride, const float *normals,
                  const uint8_t *mask);
+// True when the frame can use the flat tiles: any depth layout, normals and
+// mask that start at the same place of a 4-byte word counted in pixels (as
+// dense arrays of a stack do), W >= 4.
+bool flat_layout(int32_t W, const float *normals, const uint8_t *mask);
+// fill_frame_args' px_per_item for flat tiles: work items of four consecutive
+// pixels of the frame, rows counted in pixels.
+constexpr int kFlatItems = 0;
 // True when the method can take vector tiles (multi-scale: alpha * scales
 // <= kMsVecReach).
 bool method_has_vec4(const bn_params *p);
 // The plain entry point's tile shape when nothing is tuned for the frame:
-// vector tiles where the method and the layout allow them, except four-pair
-// frames of at most kSmallFrame pixels, which take the scalar tiles.
+// vector tiles where the method and the layout allow them, except frames of
+// at most kSmallFrame pixels (multi-scale: kSmallFrameMs), which take the
+// scalar tiles.
 constexpr uint64_t kSmallFrame = 1u << 19;
+constexpr uint64_t kSmallFrameMs = 3u << 17;
 int default_plain_variant(const bn_params *p, uint64_t pixels, bool vec_layout);
+// Where the vector tiles don't serve, single frames of more than kSmallRagged
+// pixels take the flat tiles, smaller ones the scalar tiles (one frame of few
+// tiles is a chain of latencies, shorter with more wavefronts).  Scalar
+// against flat, four-pair: 637x479 3.9 / 4.7 us, 1277x719 5.7 / 5.7, 1103x1021
+// 6.6 / 5.9, 1917x1079 9.7 / 8.2, 2555x1429 15.5 / 12.8.
+constexpr uint64_t kSmallRagged = 1u << 20;
 // Per-frame kernel arguments (derived constants included); work = NULL (the
 // caller sets the count work area when stats is given).
 void fill_frame_args(FrameArgs &f, const float *depth, int32_t H, int32_t W, int64_t stride,

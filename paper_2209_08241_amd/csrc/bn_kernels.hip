@@ -47,9 +47,18 @@ __global__ __launch_bounds__(kBlock) void k_vec4(FrameArgs f) {
     for (int g = 0; g < G; ++g) {
         const uint32_t tile = blk * G + g;
         if (tile * kBlock >= f.nitems) break;  // uniform over the workgroup
-        run_tile<A, M>(f, true, tile, lds, cv, cb);
+        run_tile<A, M, false>(f, kTileVec4, tile, lds, cv, cb);
     }
     if (f.stats) block_counts(f, blockIdx.x, gridDim.x, cv, cb);
+}
+
+// Flat kernel: four consecutive pixels of the frame per lane, any depth
+// layout and any reach (run-time offsets).
+template <int M>
+__global__ __launch_bounds__(kBlock) void k_flat(FrameArgs f) {
+    __shared__ TileLds lds;
+    const uint32_t blk = xcd_tile(blockIdx.x, gridDim.x);
+    flat_tile_counted<M>(f, blk, blockIdx.x, gridDim.x, lds);
 }
 
 // Vector kernel, two tiles per workgroup, software-pipelined (the second
@@ -139,6 +148,14 @@ const VariantInfo *variant_info(int v) {
 }
 
 hipError_t launch_plain(int variant, int method, const FrameArgs &f, hipStream_t stream) {
+    if (variant == VAR_FLAT) {
+        KernelFn flat = method == kFourPair      ? k_flat<kFourPair>
+                        : method == kPairRemoval ? k_flat<kPairRemoval>
+                                                 : k_flat<kMultiScale>;
+        hipLaunchKernelGGL(flat, dim3((f.nitems + kBlock - 1u) / kBlock), dim3(kBlock), 0, stream,
+                           f);
+        return hipGetLastError();
+    }
     const VariantInfo *vi = variant_info(variant);
     if (!vi) return hipErrorInvalidValue;
     KernelFn fn = nullptr;

@@ -25,11 +25,26 @@ __global__ __launch_bounds__(kBlock) void k_stack(const StackArgs s) {
     const uint32_t k = b / s.tiles_per_frame;
     const uint32_t tile = b - k * s.tiles_per_frame;
     const FrameArgs f = stack_frame(s, k);
-    if (s.vec) {
+    if (s.kind == kTileVec4) {
         vec4_tile_counted<A, M>(f, tile, tile, s.tiles_per_frame, lds);
         return;
     }
     scalar_tile_counted<A, M>(f, tile, tile, s.tiles_per_frame, lds);
+}
+
+// Stacks in flat tiles: frame k's positions start where its outputs do.
+// (16 frames of 637x479: 32.7 us in scalar tiles, 15.9 us; four of 1277x719 in
+// pair removal 27.4 / 16.2 us, in multi-scale with a reach of 24 39.0 / 25.1.)
+template <int M>
+__global__ __launch_bounds__(kBlock) void k_stack_flat(const StackArgs s) {
+    __shared__ TileLds lds;
+    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
+    const uint32_t k = b / s.tiles_per_frame;
+    const uint32_t tile = b - k * s.tiles_per_frame;
+    FrameArgs f = stack_frame(s, k);
+    f.shift = (f.shift + k * f.npix) & 127u;
+    f.nitems = (f.npix + f.shift + 3u) / 4u;
+    flat_tile_counted<M>(f, tile, tile, s.tiles_per_frame, lds);
 }
 
 typedef void (*StackFn)(const StackArgs);
@@ -49,11 +64,16 @@ static StackFn stack_kernel_m(int alpha) {
     return nullptr;
 }
 
-static StackFn stack_kernel(int method, int alpha, int scales, bool vec) {
+static StackFn stack_kernel(int method, int alpha, int scales, uint32_t kind) {
+    if (kind == kTileFlat) {
+        return method == kFourPair      ? k_stack_flat<kFourPair>
+               : method == kPairRemoval ? k_stack_flat<kPairRemoval>
+                                        : k_stack_flat<kMultiScale>;
+    }
     if (method == kFourPair) return stack_kernel_m<kFourPair>(alpha);
     if (method == kPairRemoval) return stack_kernel_m<kPairRemoval>(alpha);
     // multi-scale scalar tiles take the offsets at run time
-    if (method == kMultiScale && !vec) return k_stack<1, kMultiScale>;
+    if (method == kMultiScale && kind != kTileVec4) return k_stack<1, kMultiScale>;
     if (kernel_method(method, alpha, scales) == kMultiScaleLong)
         return stack_kernel_m<kMultiScaleLong>(alpha);
     if (method == kMultiScale) return stack_kernel_m<kMultiScale>(alpha);
@@ -114,20 +134,29 @@ extern "C" int bn_estimate_normals_stack(const float *depth, int32_t n, int32_t 
     const bool vec_ok = method_has_vec4(params) && (n == 1 || depth_frame_stride % 4 == 0) &&
                         vec4_layout(depth, width, depth_stride, normals, mask);
     if (v == VAR_VEC4 && !vec_ok) return BN_ERR_UNSUPPORTED;
-    const bool vec = v == VAR_VEC4 || (v == VAR_AUTO && vec_ok);
-    if (vec) {
-        rc = stack_args(s, depth, n, height, width, depth_stride, depth_frame_stride, intrinsics,
-                        params, normals, mask, stats, 4);
-        if (rc != BN_OK) return rc;
+    s.kind = kTileScalar;
+    if (v == VAR_VEC4 || (v == VAR_AUTO && vec_ok)) {
+        s.kind = kTileVec4;
+    } else if (v == VAR_AUTO && flat_layout(width, normals, mask)) {
+        s.kind = kTileFlat;
     }
-    StackFn fn = stack_kernel(params->method, params->alpha, params->scales, vec);
+    if (s.kind != kTileScalar) {
+        const uint32_t kind = s.kind;
+        rc = stack_args(s, depth, n, height, width, depth_stride, depth_frame_stride, intrinsics,
+                        params, normals, mask, stats, kind == kTileVec4 ? 4 : kFlatItems);
+        if (rc != BN_OK) return rc;
+        s.kind = kind;
+    }
+    StackFn fn = stack_kernel(params->method, params->alpha, params->scales, s.kind);
     if (!fn) return BN_ERR_UNSUPPORTED;
     if (stats) {
         rc = stream_work_areas((hipStream_t)stream, &s.f.work);
         if (rc != BN_OK) return rc;
     }
-    s.vec = vec ? 1u : 0u;
-    s.tiles_per_frame = (s.f.nitems + kBlock - 1) / kBlock;
+    // a flat tile's first position differs from frame to frame: the most tiles
+    // that a frame takes
+    const uint32_t items = s.kind == kTileFlat ? (s.f.npix + 127u + 3u) / 4u : s.f.nitems;
+    s.tiles_per_frame = (items + kBlock - 1) / kBlock;
     const uint64_t grid = (uint64_t)s.tiles_per_frame * s.n;
     hipLaunchKernelGGL(fn, dim3((uint32_t)grid), dim3(kBlock), 0, (hipStream_t)stream, s);
     return hipGetLastError() == hipSuccess ? BN_OK : BN_ERR_DEVICE;

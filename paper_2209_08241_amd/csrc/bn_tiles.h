@@ -418,18 +418,288 @@ __device__ __forceinline__ void scalar_count(const ScalarOut &r, uint32_t &cv, u
     cb += wave_count(r.live & (r.code == BN_BOUNDARY));
 }
 
-// One whole tile of either kind, method M.  No workgroup barrier:
+// ---------------------------------------------------------------------------
+// Flat tile: four consecutive pixels of the frame per lane, for any width,
+// row stride and depth alignment (multiples of 4 bytes), and any reach.  Work
+// item i is the pixels 4i - shift .. 4i - shift + 3 of the dense outputs
+// (those that are in the frame), with `shift` such that a wavefront's outputs
+// are whole 128-byte lines, wherever the outputs start: streaming stores of
+// partial lines cost twice the time (a 2555x1429 frame by segments of rows,
+// whose stores start anywhere, 22.9 us; by flat tiles 12.8 us; by scalar
+// tiles, one pixel per thread, 15.5 us).  All taps are loads of their own, the
+// horizontal ones at x - alpha and x + alpha: a 16-byte load needs 4-byte
+// alignment only, and the lines are in L1.
+//
+// Bounds: a lane whose four pixels lie in one row loads rows y, y - alpha and
+// y + alpha (row y itself where those leave the frame) at x, within the row,
+// and row y at x +- alpha, which may run into the neighbouring row's memory
+// (it exists, or the start is clamped into the row); what that brings in
+// only reaches pixels that are not inside.  A lane whose pixels run over a
+// row's end (or the frame's start or end) takes the taps of its pixels that
+// are inside one by one.  Needs W >= 4.
+// ---------------------------------------------------------------------------
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ f4 load4(const float *p) { return *reinterpret_cast<const f4u *>(p); }
+
+// The depth at (x, y), clamped into the frame.
+__device__ __forceinline__ float tap_clamped(const FrameArgs &f, int x, int y) {
+    x = min(max(x, 0), f.W - 1);
+    y = min(max(y, 0), f.H - 1);
+    return f.depth[(int64_t)y * f.stride + x];
+}
+
+// First pixel of work item i (below 2^28 + 2^8; negative or past the end:
+// not in the frame).
+__device__ __forceinline__ int flat_pos(const FrameArgs &f, uint32_t i) {
+    return (int)(4u * i) - (int)f.shift;
+}
+
+// The lane's pixels: first one's row and column, and those of pixel j (row -1
+// before the frame's first pixel, row H after its last one).
+struct FlatPos {
+    int x, y;
+    bool split;  // the pixels run over the row's end
+    __device__ __forceinline__ int xj(int j, int W) const {
+        return split && x + j >= W ? x + j - W : x + j;
+    }
+    __device__ __forceinline__ int yj(int j, int W) const {
+        return split && x + j >= W ? y + 1 : y;
+    }
+};
+
+template <int M>
+__device__ __forceinline__ void flat_eval(const FrameArgs &f, uint32_t tile, Vec4Out &o,
+                                          TileLds &lds) {
+    const uint32_t t = threadIdx.x;
+    const int W = f.W, H = f.H;
+    // lanes past either end of the frame take its first or last position
+    const int p0 = min(max(flat_pos(f, tile * kBlock + t), -3), (int)f.npix - 1);
+    FlatPos q;
+    q.y = p0 >= 0 ? (int)row_of((uint32_t)p0, f.inv_gpr) : -1;
+    q.x = p0 - q.y * W;
+    q.split = q.x + 4 > W;
+    // the whole wavefront's question: does any lane hold two rows?
+    const bool any_split = __builtin_amdgcn_ballot_w64(q.split) != 0;
+    const int xl = min(q.x, W - 4);  // a split lane's vector loads are not used
+    const int yr = max(q.y, 0);
+    const float *rp = f.depth + (int64_t)yr * f.stride;
+    const int xmin = yr > 0 ? -3 : 0;
+    const int xmax = yr + 1 < H ? W - 1 : W - 4;
+    float xc[4], yc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        xc[j] = (float)(q.x + j) - f.cx;
+        yc[j] = (float)q.y - f.cy;
+    }
+    uint32_t codes = 0;
+    float *st = reinterpret_cast<float *>(lds.v + 192 * (t >> 6)) + 12 * (t & 63u);
+    if constexpr (is_multiscale(M)) {
+        const int reach = f.scales * f.alpha;
+        const f4 c = load4(rp + xl);
+        const float d1[4] = {c.x, c.y, c.z, c.w};
+        const bool rows_in = yr + reach < H;
+        bool ok[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            ok[j] = rows_in & (q.x + j + reach < W) & (tap_ok(d1[j]) != 0u);
+        float Mx[4] = {0.f, 0.f, 0.f, 0.f}, My[4] = {0.f, 0.f, 0.f, 0.f};
+        float Mz[4] = {0.f, 0.f, 0.f, 0.f}, Wt[4] = {0.f, 0.f, 0.f, 0.f};
+        // the taps of kBatch scales are loaded before their arithmetic
+        constexpr int kBatch = 2;
+        const float *bp = rp + xl;
+        const int64_t step = rows_in ? (int64_t)f.alpha * f.stride : 0;
+        int off = f.alpha;
+        for (int s0 = 1; s0 <= f.scales; s0 += kBatch) {
+            f4 r2[kBatch], r3[kBatch];
+#pragma unroll
+            for (int s = 0; s < kBatch; ++s) {
+                if (s0 + s > f.scales) break;
+                bp += step;
+                r2[s] = load4(rp + min(q.x + off + s * f.alpha, xmax));
+                r3[s] = load4(bp);
+            }
+#pragma unroll
+            for (int s = 0; s < kBatch; ++s) {
+                if (s0 + s > f.scales) break;
+                const float d2[4] = {r2[s].x, r2[s].y, r2[s].z, r2[s].w};
+                const float d3[4] = {r3[s].x, r3[s].y, r3[s].z, r3[s].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    ok[j] = ok[j] & ((tap_ok(d2[j]) & tap_ok(d3[j])) != 0u);
+                    ms_accumulate(d1[j], d2[j], d3[j], (float)off, xc[j], yc[j], f, Mx[j], My[j],
+                                  Mz[j], Wt[j]);
+                }
+                off += f.alpha;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            PixelOut p = ms_finish(ok[j] ? 1u : 0u, Mx[j], My[j], Mz[j], Wt[j], f);
+            if (any_split) {
+                if (q.split) {
+                    const int x = q.xj(j, W), y = max(q.yj(j, W), 0);
+                    const bool inside = (x + reach < W) & (y + reach < H);
+                    p = eval_pixel_multiscale(
+                        inside, f.depth + (int64_t)min(y, H - 1) * f.stride + x, (float)x - f.cx,
+                        (float)y - f.cy, f);
+                }
+            }
+            o.nv[3 * j + 0] = p.nx;
+            o.nv[3 * j + 1] = p.ny;
+            o.nv[3 * j + 2] = p.nz;
+            codes |= p.code << (8 * j);
+        }
+    } else {
+        const int a = f.alpha;
+        const f4 c = load4(rp + xl);
+        const f4 up = load4(rp - (yr >= a ? (int64_t)a * f.stride : 0) + xl);
+        const f4 dn = load4(rp + (yr + a < H ? (int64_t)a * f.stride : 0) + xl);
+        const f4 lt = load4(rp + max(xl - a, xmin));
+        const f4 rt = load4(rp + min(q.x + a, xmax));
+        float d1[4] = {c.x, c.y, c.z, c.w}, d2[4] = {rt.x, rt.y, rt.z, rt.w};
+        float d3[4] = {dn.x, dn.y, dn.z, dn.w}, d4[4] = {lt.x, lt.y, lt.z, lt.w};
+        float d5[4] = {up.x, up.y, up.z, up.w};
+        bool in[4];
+        const bool rows_in = (q.y >= a) & (q.y + a < H);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) in[j] = rows_in & (q.x + j >= a) & (q.x + j + a < W);
+        if (any_split) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int x = q.xj(j, W), y = q.yj(j, W);
+                xc[j] = (float)x - f.cx;
+                yc[j] = (float)y - f.cy;
+                in[j] = (x >= a) & (x + a < W) & (y >= a) & (y + a < H);
+                // none for alpha >= 3: the four pixels are in the border
+                if (q.split & in[j]) {
+                    const float *px = f.depth + (int64_t)y * f.stride + x;
+                    d1[j] = px[0];
+                    d2[j] = px[a];
+                    d4[j] = px[-a];
+                    d3[j] = px[(int64_t)a * f.stride];
+                    d5[j] = px[-(int64_t)a * f.stride];
+                }
+            }
+        }
+        if (kEarlyStage<M>) wave_lds_sync();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const PixelOut p = eval_method<M>(in[j], d1[j], d2[j], d3[j], d4[j], d5[j], xc[j],
+                                              yc[j], f);
+            if (kEarlyStage<M>) {
+                st[3 * j + 0] = p.nx;
+                st[3 * j + 1] = p.ny;
+                st[3 * j + 2] = p.nz;
+            } else {
+                o.nv[3 * j + 0] = p.nx;
+                o.nv[3 * j + 1] = p.ny;
+                o.nv[3 * j + 2] = p.nz;
+            }
+            codes |= p.code << (8 * j);
+        }
+    }
+    o.codes = codes;
+}
+
+// The wavefront's outputs: as vec4_write, for a frame that may start or end
+// within a lane's four pixels (those floats and bytes are stored one by one).
+template <int M>
+__device__ __forceinline__ void flat_write(const FrameArgs &f, uint32_t tile, TileLds &lds,
+                                           const Vec4Out &o) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const float *nv = o.nv;
+    const uint32_t w = wave_id();
+    const int p0 = flat_pos(f, tile * kBlock + 64u * w);  // the wavefront's first position
+    // its positions lo .. hi-1 are pixels of the frame
+    const int lo = min(max(-p0, 0), 256), hi = max(min((int)f.npix - p0, 256), lo);
+    uint8_t *mask = f.mask + p0;
+    float *n = f.normals + 3 * (int64_t)p0;
+    const int b0 = (lo + 3) & ~3, b1 = max(hi & ~3, b0);  // bytes in whole words
+    const int g0 = (3 * lo + 3) & ~3, g1 = max((3 * hi) & ~3, g0);  // floats in whole float4s
+    // (offsets below the resource's base go past its size and are dropped)
+    constexpr uint32_t kDrop = 1u << 30;
+    out_store(o.codes, out_buf(mask + b0, (uint32_t)(b1 - b0)),
+              min(4u * lane - (uint32_t)b0, kDrop));
+    f4 *slice = lds.v + 192 * w;
+    if (!kEarlyStage<M>) {
+        wave_lds_sync();
+        slice[3 * lane + 0] = f4{nv[0], nv[1], nv[2], nv[3]};
+        slice[3 * lane + 1] = f4{nv[4], nv[5], nv[6], nv[7]};
+        slice[3 * lane + 2] = f4{nv[8], nv[9], nv[10], nv[11]};
+    }
+    wave_lds_sync();
+    const OutBuf nb = out_buf(n + g0, 4u * (uint32_t)(g1 - g0));
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        out_store(slice[64 * k + lane], nb,
+                  min(16u * lane + 1024u * k - 4u * (uint32_t)g0, kDrop));
+    if (((lo | hi) & 3) != 0) {  // the frame starts or ends within a lane's pixels
+        const float *sf = reinterpret_cast<const float *>(slice);
+        for (int k = 3 * lo + (int)lane; k < 3 * hi; k += 64)
+            if (k < g0 || k >= g1) n[k] = sf[k];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = 4 * (int)lane + j;
+            if (k >= lo && k < hi && (k < b0 || k >= b1)) mask[k] = (uint8_t)(o.codes >> (8 * j));
+        }
+    }
+}
+
+__device__ __forceinline__ void flat_count(const FrameArgs &f, uint32_t tile, const Vec4Out &o,
+                                           uint32_t &cv, uint32_t &cb) {
+    const int p0 = flat_pos(f, tile * kBlock + threadIdx.x);
+    const uint32_t codes = o.codes;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint64_t lm = __builtin_amdgcn_ballot_w64((uint32_t)(p0 + j) < f.npix);
+        const uint32_t c = (codes >> (8 * j)) & 0xffu;
+        cv += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(c == BN_VALID) & lm);
+        cb += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(c == BN_BOUNDARY) & lm);
+    }
+}
+
+// One flat tile with its counts, as part `part` of `nparts` of the frame.
+template <int M>
+__device__ __forceinline__ void flat_tile_counted(const FrameArgs &f, uint32_t tile, uint32_t part,
+                                                  uint32_t nparts, TileLds &lds) {
+    Vec4Out o;
+    flat_eval<M>(f, tile, o, lds);
+    CountTicket tk;
+    bool have = false;
+    uint32_t cv = 0, cb = 0;
+    flat_count(f, tile, o, cv, cb);
+    if (f.stats) {
+        uint32_t v, b;
+        block_sum(cv, cb, v, b);
+        if (threadIdx.x == 0) {
+            tk = count_issue(f.work, f.stats, part, nparts, v, b, f.npix, f.overwrite);
+            have = true;
+        }
+    }
+    flat_write<M>(f, tile, lds, o);
+    if (have) count_finish(tk);
+}
+
+// One whole tile of any kind, method M.  No workgroup barrier:
 // consecutive tiles of a workgroup may overlap freely.  The multi-scale
 // method takes vector tiles only when alpha * scales <= kMsVecReach (the host's
 // choice).
-template <int A, int M>
-__device__ __forceinline__ void run_tile(const FrameArgs &f, bool vec, uint32_t tile, TileLds &lds,
-                                         uint32_t &cv, uint32_t &cb) {
-    if (vec) {
+// FLAT: kind may be kTileFlat (the flat body's registers would otherwise cost
+// the others wavefronts).
+template <int A, int M, bool FLAT>
+__device__ __forceinline__ void run_tile(const FrameArgs &f, uint32_t kind, uint32_t tile,
+                                         TileLds &lds, uint32_t &cv, uint32_t &cb) {
+    if (kind == kTileVec4) {
         Vec4Out o;
         vec4_eval_method<A, M>(f, tile, o, lds);
         vec4_write<M>(f, tile, lds, o);
         if (f.stats) vec4_count(o, cv, cb);
+    } else if (FLAT && kind == kTileFlat) {
+        Vec4Out o;
+        flat_eval<M>(f, tile, o, lds);
+        flat_write<M>(f, tile, lds, o);
+        if (f.stats) flat_count(f, tile, o, cv, cb);
     } else {
         ScalarOut r;
         scalar_eval<A, M>(f, tile, r);
