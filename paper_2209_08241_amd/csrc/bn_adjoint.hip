@@ -17,13 +17,13 @@
 // its gradient is ((g2 + g4) + g3) + g5 of those four pixels, in that order
 // in every kernel here, so all of them give the same bits.
 //
-// Vector kernels (rows of whole float4 groups, a <= 4): a workgroup owns a
-// strip of 56 float4 groups (224 columns: the strip's gradient rows start on
-// 128-byte lines, and so do its cotangent rows) and a band of NW RB rows,
-// RB rows per wavefront, NW = 4 or 8 wavefronts.  Lane l evaluates group
-// 56 s - 4 + l of each row (its
-// codes and tap gradients, from float4 loads), so lanes 4..59 own the
-// strip's outputs and lanes 3 and 60 are the halo; the horizontal taps and
+// Vector kernels (a <= 4): a workgroup owns a strip of 56 float4 groups (224
+// columns: on aligned rows the strip's gradient rows start on 128-byte lines,
+// and so do its cotangent rows) and a band of NW RB rows, RB rows per
+// wavefront, NW = 4 or 8 wavefronts.  Lane l evaluates group 56 s - 4 + l of
+// each row (its codes and tap gradients, from 16-byte loads, which need
+// 4-byte alignment only), so lanes 4..59 own the strip's outputs and lanes 3
+// and 60 are the halo; the horizontal taps and
 // the tap-2 / tap-4 gradients move between neighbouring lanes by DPP.  Each
 // wavefront rolls down its rows keeping the last 2a rows' gradients in
 // registers; the a rows next to a neighbouring wavefront's rows are finished
@@ -189,9 +189,11 @@ struct RowGrads {
 };
 
 // The loads of one row: the depth of the lane's group in rows y, y-a and
-// y+a, the halo lanes' outer group of row y, and the cotangents.
+// y+a, and the cotangents.  (What lanes 0 and 63 would need from beyond the
+// wavefront only reaches their own and their neighbours' gradients, which no
+// output lane reads.)
 struct RowLoad {
-    f4 c, up, dn, side, k0, k1, k2;
+    f4 c, up, dn, k0, k1, k2;
 };
 
 __device__ __forceinline__ bool vjp4_row_live(const FrameArgs &f, int y, int a) {
@@ -203,35 +205,40 @@ __device__ __forceinline__ bool vjp4_row_live(const FrameArgs &f, int y, int a) 
 // into the frame.  Every load in a row is unconditional (a clamped lane
 // loads some group of the row); the values a clamped load brings in only
 // reach pixels that are not inside, whose codes are INVALID and whose
-// gradients are therefore zero.
-template <int A>
+// gradients are therefore zero.  Where the row's last group is not whole
+// (RAGGED), its lanes' loads run into the next row's memory, which exists
+// except after the frame's last row of depth: that one is read element by
+// element, clamped.
+template <int A, bool RAGGED>
 __device__ __forceinline__ void vjp4_load(const FrameArgs &f, const float *__restrict__ gn, int y,
-                                          int x0, int xl, uint32_t lane, RowLoad &L) {
+                                          int xl, RowLoad &L) {
     if (!vjp4_row_live(f, y, A)) return;
     const float *rp = f.depth + (int64_t)y * f.stride;
-    L.c = *reinterpret_cast<const f4 *>(rp + xl);
-    L.up = *reinterpret_cast<const f4 *>(rp - (int64_t)A * f.stride + xl);
-    L.dn = *reinterpret_cast<const f4 *>(rp + (int64_t)A * f.stride + xl);
-    const f4 *gp = reinterpret_cast<const f4 *>(gn + 3 * (int64_t)y * f.W) + 3 * (xl >> 2);
-    L.k0 = gp[0];
-    L.k1 = gp[1];
-    L.k2 = gp[2];
-    if (lane == 0) L.side = *reinterpret_cast<const f4 *>(rp + max(x0 - 4, 0));
-    if (lane == 63) L.side = *reinterpret_cast<const f4 *>(rp + min(x0 + 4, f.W - 4));
+    const float *dp = rp + (int64_t)A * f.stride;
+    L.c = load4(rp + xl);
+    L.up = load4(rp - (int64_t)A * f.stride + xl);
+    if (RAGGED && y + A + 1 == f.H) {
+        L.dn = f4{dp[xl], dp[min(xl + 1, f.W - 1)], dp[min(xl + 2, f.W - 1)],
+                  dp[min(xl + 3, f.W - 1)]};
+    } else {
+        L.dn = load4(dp + xl);
+    }
+    const float *gp = gn + 3 * ((int64_t)y * f.W + xl);
+    L.k0 = load4(gp);
+    L.k1 = load4(gp + 4);
+    L.k2 = load4(gp + 8);
 }
 
 template <int A>
-__device__ __forceinline__ RowGrads vjp4_eval(const FrameArgs &f, int y, int x0, uint32_t lane,
+__device__ __forceinline__ RowGrads vjp4_eval(const FrameArgs &f, int y, int x0,
                                               const RowLoad &L) {
     RowGrads r;
     r.h = r.g3 = r.g5 = f4{0.f, 0.f, 0.f, 0.f};
     if (!vjp4_row_live(f, y, A)) return r;
     const bool gin = (x0 >= 0) & (x0 < f.W);
     const f4 c = L.c, up = L.up, dn = L.dn, k0 = L.k0, k1 = L.k1, k2 = L.k2;
-    // Row window x0-4 .. x0+7 (the halo lanes loaded their outer float4).
-    f4 lk = from_left(c), rk = from_right(c);
-    if (lane == 0) lk = L.side;
-    if (lane == 63) rk = L.side;
+    // Row window x0-4 .. x0+7
+    const f4 lk = from_left(c), rk = from_right(c);
     const float row[12] = {lk.x, lk.y, lk.z, lk.w, c.x, c.y, c.z, c.w, rk.x, rk.y, rk.z, rk.w};
     const float upv[4] = {up.x, up.y, up.z, up.w};
     const float dnv[4] = {dn.x, dn.y, dn.z, dn.w};
@@ -265,16 +272,16 @@ __device__ __forceinline__ RowGrads vjp4_eval(const FrameArgs &f, int y, int x0,
     return r;
 }
 
-template <int A>
+template <int A, bool RAGGED>
 __device__ __forceinline__ RowGrads vjp4_row(const FrameArgs &f, const float *__restrict__ gn,
-                                             int y, int x0, int xl, uint32_t lane) {
+                                             int y, int x0, int xl) {
     RowLoad L;
-    vjp4_load<A>(f, gn, y, x0, xl, lane, L);
-    return vjp4_eval<A>(f, y, x0, lane, L);
+    vjp4_load<A, RAGGED>(f, gn, y, xl, L);
+    return vjp4_eval<A>(f, y, x0, L);
 }
 
 // Strip `strip`, band `band` of one frame (see the top of the file).
-template <int A, int RB, int NW>
+template <int A, int RB, int NW, bool RAGGED>
 __device__ __forceinline__ void vjp4_band(const FrameArgs &f, const float *__restrict__ gn,
                                           float *__restrict__ gd, uint32_t strip,
                                           uint32_t band) {
@@ -287,31 +294,44 @@ __device__ __forceinline__ void vjp4_band(const FrameArgs &f, const float *__res
     // the wavefront index, uniform: row addresses and bounds are scalar
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int x0 = 4 * ((int)(strip * kVjpGroups + lane) - kVjpLead);
-    const int xl = min(max(x0, 0), f.W - 4);
+    const int xl = min(max(x0, 0), f.W - (RAGGED ? 1 : 4));
     const int y0 = (int)(band * (uint32_t)(NW * RB));
     const int yw = y0 + (int)w * RB;
     const bool out_lane = (lane >= (uint32_t)kVjpLead) &
                           (lane < (uint32_t)(kVjpLead + kVjpGroups)) & (x0 < f.W);
     auto put = [&](int y, f4 v) {
-        if (out_lane && y < f.H)
+        if (!(out_lane && y < f.H)) return;
+        if (!RAGGED) {
             out_store(v, out_buf(gd + (int64_t)y * f.W, 4u * (uint32_t)f.W), 4u * (uint32_t)x0);
+            return;
+        }
+        // rows that start anywhere: stores through L2, which joins the parts
+        // of a line that neighbouring strips write
+        float *g = gd + (int64_t)y * f.W + x0;
+        if (x0 + 4 <= f.W) {
+            *reinterpret_cast<f4u *>(g) = v;
+            return;
+        }
+        g[0] = v.x;
+        if (x0 + 1 < f.W) g[1] = v.y;
+        if (x0 + 2 < f.W) g[2] = v.z;
     };
     // The band's 2a outer rows, dealt round the wavefronts.
     for (int k = (int)w; k < 2 * A; k += NW) {
         if (k < A) {
-            x3[0][k][lane] = vjp4_row<A>(f, gn, y0 - A + k, x0, xl, lane).g3;
+            x3[0][k][lane] = vjp4_row<A, RAGGED>(f, gn, y0 - A + k, x0, xl).g3;
         } else {
-            x5[NW][k - A][lane] = vjp4_row<A>(f, gn, y0 + NW * RB + (k - A), x0, xl, lane).g5;
+            x5[NW][k - A][lane] = vjp4_row<A, RAGGED>(f, gn, y0 + NW * RB + (k - A), x0, xl).g5;
         }
     }
     f4 h[RB], g3[RB], top5[A], bot[A];
     // each row's loads are issued before the previous row is evaluated
     RowLoad cur, nxt;
-    vjp4_load<A>(f, gn, yw, x0, xl, lane, cur);
+    vjp4_load<A, RAGGED>(f, gn, yw, xl, cur);
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
-        if (i + 1 < RB) vjp4_load<A>(f, gn, yw + i + 1, x0, xl, lane, nxt);
-        const RowGrads e = vjp4_eval<A>(f, yw + i, x0, lane, cur);
+        if (i + 1 < RB) vjp4_load<A, RAGGED>(f, gn, yw + i + 1, xl, nxt);
+        const RowGrads e = vjp4_eval<A>(f, yw + i, x0, cur);
         cur = nxt;
         h[i] = e.h;
         g3[i] = e.g3;
@@ -329,21 +349,21 @@ __device__ __forceinline__ void vjp4_band(const FrameArgs &f, const float *__res
     for (int j = 0; j < A; ++j) put(yw + RB - A + j, bot[j] + x5[w + 1][j][lane]);
 }
 
-template <int A, int RB, int NW>
+template <int A, int RB, int NW, bool RAGGED>
 __global__ __launch_bounds__(64 * NW) void k_vjp4(FrameArgs f, const float *__restrict__ gn,
                                                   float *__restrict__ gd, uint32_t strips) {
     const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    vjp4_band<A, RB, NW>(f, gn, gd, b % strips, b / strips);
+    vjp4_band<A, RB, NW, RAGGED>(f, gn, gd, b % strips, b / strips);
 }
 
 // A stack: workgroup b takes band-strip b % T of frame b / T.
-template <int A, int RB, int NW>
+template <int A, int RB, int NW, bool RAGGED>
 __global__ __launch_bounds__(64 * NW) void k_vjp4_stack(const StackArgs s) {
     const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
     const uint32_t k = b / s.tiles_per_frame;
     const uint32_t t = b - k * s.tiles_per_frame;
     const int64_t npix = (int64_t)s.f.npix;
-    vjp4_band<A, RB, NW>(stack_frame(s, k), s.gn + (int64_t)k * npix * 3,
+    vjp4_band<A, RB, NW, RAGGED>(stack_frame(s, k), s.gn + (int64_t)k * npix * 3,
                          s.gd + (int64_t)k * npix, t % s.tiles_x, t / s.tiles_x);
 }
 
@@ -366,7 +386,7 @@ struct Vjp4Shape {
 
 static Vjp4Shape vjp4_shape(int32_t H, int32_t W, int32_t n, int alpha) {
     Vjp4Shape s;
-    s.strips = (uint32_t)((W / 4 + kVjpGroups - 1) / kVjpGroups);
+    s.strips = (uint32_t)(((W + 3) / 4 + kVjpGroups - 1) / kVjpGroups);
     s.rb = alpha <= 2 ? 4 : 8;
     const uint64_t wide = (uint64_t)s.strips * (uint64_t)((H + 8 * s.rb - 1) / (8 * s.rb)) * n;
     s.nw = wide >= kVjpWide ? 8 : 4;
@@ -377,43 +397,59 @@ static Vjp4Shape vjp4_shape(int32_t H, int32_t W, int32_t n, int alpha) {
 typedef void (*Vjp4Fn)(FrameArgs, const float *, float *, uint32_t);
 typedef void (*Vjp4StackFn)(const StackArgs);
 
-template <int NW>
+template <int NW, bool RAGGED>
 static Vjp4Fn vjp4_kernel_w(int a) {
     switch (a) {
-        case 1: return k_vjp4<1, 4, NW>;
-        case 2: return k_vjp4<2, 4, NW>;
-        case 3: return k_vjp4<3, 8, NW>;
-        case 4: return k_vjp4<4, 8, NW>;
+        case 1: return k_vjp4<1, 4, NW, RAGGED>;
+        case 2: return k_vjp4<2, 4, NW, RAGGED>;
+        case 3: return k_vjp4<3, 8, NW, RAGGED>;
+        case 4: return k_vjp4<4, 8, NW, RAGGED>;
     }
     return nullptr;
 }
 
-template <int NW>
+template <int NW, bool RAGGED>
 static Vjp4StackFn vjp4_stack_kernel_w(int a) {
     switch (a) {
-        case 1: return k_vjp4_stack<1, 4, NW>;
-        case 2: return k_vjp4_stack<2, 4, NW>;
-        case 3: return k_vjp4_stack<3, 8, NW>;
-        case 4: return k_vjp4_stack<4, 8, NW>;
+        case 1: return k_vjp4_stack<1, 4, NW, RAGGED>;
+        case 2: return k_vjp4_stack<2, 4, NW, RAGGED>;
+        case 3: return k_vjp4_stack<3, 8, NW, RAGGED>;
+        case 4: return k_vjp4_stack<4, 8, NW, RAGGED>;
     }
     return nullptr;
 }
 
-static Vjp4Fn vjp4_kernel(const Vjp4Shape &sh, int a) {
-    return sh.nw == 8 ? vjp4_kernel_w<8>(a) : vjp4_kernel_w<4>(a);
+static Vjp4Fn vjp4_kernel(const Vjp4Shape &sh, int a, bool ragged) {
+    if (ragged) return sh.nw == 8 ? vjp4_kernel_w<8, true>(a) : vjp4_kernel_w<4, true>(a);
+    return sh.nw == 8 ? vjp4_kernel_w<8, false>(a) : vjp4_kernel_w<4, false>(a);
 }
 
-static Vjp4StackFn vjp4_stack_kernel(const Vjp4Shape &sh, int a) {
-    return sh.nw == 8 ? vjp4_stack_kernel_w<8>(a) : vjp4_stack_kernel_w<4>(a);
+static Vjp4StackFn vjp4_stack_kernel(const Vjp4Shape &sh, int a, bool ragged) {
+    if (ragged)
+        return sh.nw == 8 ? vjp4_stack_kernel_w<8, true>(a) : vjp4_stack_kernel_w<4, true>(a);
+    return sh.nw == 8 ? vjp4_stack_kernel_w<8, false>(a) : vjp4_stack_kernel_w<4, false>(a);
 }
 
 static bool aligned16(const void *p) { return ((uintptr_t)p % 16) == 0; }
 
-// The vector kernels' layout: rows of whole, 16-byte aligned float4 groups.
-static bool vjp4_layout(const float *depth, int32_t W, int64_t stride, int64_t fstride,
-                        const float *gn, const float *gd, int alpha) {
-    return alpha <= 4 && W % 4 == 0 && stride % 4 == 0 && fstride % 4 == 0 && aligned16(depth) &&
-           aligned16(gn) && aligned16(gd);
+// The vector kernels take alpha <= 4 and rows of at least a group; rows of
+// whole, 16-byte aligned groups with streaming stores, any others as RAGGED.
+// Launches of few pixels stay with the scalar tiles: a band is a chain of RB
+// rows (2 alpha of them before its first output), and there are too few of
+// them to hide it (scalar against vector: alpha 2, 320x240 3.9 / 6.2 us,
+// 640x480 5.3 / 6.4, two of them 8.4 / 7.4, 1280x720 10.0 / 8.8; alpha 4,
+// 640x480 6.7 / 10.8, two 10.6 / 11.7, 1280x720 12.9 / 11.9).  As scalar
+// tiles, ragged frames took: four of 1277x719, alpha 1..4, 26.7, 29.0, 36.7 and
+// 38.4 us; now 21.3, 21.3, 22.3 and 23.1.
+static bool vjp4_serves(int32_t n, int32_t H, int32_t W, int alpha) {
+    return alpha <= 4 && W >= 4 &&
+           (int64_t)n * H * W > (alpha <= 2 ? (int64_t)3 << 17 : (int64_t)3 << 18);
+}
+
+static bool vjp4_ragged(const float *depth, int32_t W, int64_t stride, int64_t fstride,
+                        const float *gn, const float *gd) {
+    return !(W % 4 == 0 && stride % 4 == 0 && fstride % 4 == 0 && aligned16(depth) &&
+             aligned16(gn) && aligned16(gd));
 }
 
 typedef void (*VjpFn)(FrameArgs, const float *, float *, uint32_t);
@@ -469,9 +505,11 @@ extern "C" int bn_normals_vjp(const float *depth, int32_t height, int32_t width,
     if (rc != BN_OK) return rc;
     if (height == 0 || width == 0) return BN_OK;
     if ((uintptr_t)grad_depth % 4) return BN_ERR_INVALID_ARG;
-    if (vjp4_layout(depth, width, depth_stride, 0, grad_normals, grad_depth, params->alpha)) {
+    if (vjp4_serves(1, height, width, params->alpha)) {
         const Vjp4Shape sh = vjp4_shape(height, width, 1, params->alpha);
-        Vjp4Fn fn = vjp4_kernel(sh, params->alpha);
+        Vjp4Fn fn = vjp4_kernel(sh, params->alpha,
+                                vjp4_ragged(depth, width, depth_stride, 0, grad_normals,
+                                            grad_depth));
         if (!fn) return BN_ERR_UNSUPPORTED;
         FrameArgs f;
         fill_frame_args(f, depth, height, width, depth_stride, fx, fy, cx, cy, params, nullptr,
@@ -513,10 +551,12 @@ extern "C" int bn_normals_vjp_stack(const float *depth, int32_t n, int32_t heigh
     s.f.mask = nullptr;
     s.gn = grad_normals;
     s.gd = grad_depth;
-    if (vjp4_layout(depth, width, depth_stride, depth_frame_stride, grad_normals, grad_depth,
-                    params->alpha)) {
+    if (vjp4_serves(n, height, width, params->alpha)) {
         const Vjp4Shape sh = vjp4_shape(height, width, s.n, params->alpha);
-        Vjp4StackFn fn = vjp4_stack_kernel(sh, params->alpha);
+        Vjp4StackFn fn = vjp4_stack_kernel(sh, params->alpha,
+                                           vjp4_ragged(depth, width, depth_stride,
+                                                       depth_frame_stride, grad_normals,
+                                                       grad_depth));
         if (!fn) return BN_ERR_UNSUPPORTED;
         s.tiles_x = sh.strips;
         s.tiles_per_frame = sh.strips * sh.bands;

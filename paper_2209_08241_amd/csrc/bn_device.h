@@ -489,6 +489,11 @@ __device__ __forceinline__ void out_store_byte(uint8_t v, const OutBuf &b, uint3
     __builtin_amdgcn_raw_buffer_store_b8(v, b.r, off, 0, kOutPolicy);
 }
 
+// Four floats at any 4-byte alignment (one 16-byte load).
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ f4 load4(const float *p) { return *reinterpret_cast<const f4u *>(p); }
+
 // ---------------------------------------------------------------------------
 // Wavefront lane shifts (DPP wave_shr:1 / wave_shl:1).  Lane i receives the
 // value of lane i-1 (from_left) or i+1 (from_right); the lane without a

@@ -438,10 +438,6 @@ __device__ __forceinline__ void scalar_count(const ScalarOut &r, uint32_t &cv, u
 // row's end (or the frame's start or end) takes the taps of its pixels that
 // are inside one by one.  Needs W >= 4.
 // ---------------------------------------------------------------------------
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-
-__device__ __forceinline__ f4 load4(const float *p) { return *reinterpret_cast<const f4u *>(p); }
-
 // The depth at (x, y), clamped into the frame.
 __device__ __forceinline__ float tap_clamped(const FrameArgs &f, int x, int y) {
     x = min(max(x, 0), f.W - 1);
