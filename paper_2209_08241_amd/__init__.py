@@ -9,7 +9,9 @@ present, the calls raise.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
+import struct
 from typing import Optional, Sequence, Tuple
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -49,6 +51,19 @@ class FrameStats(ctypes.Structure):
                 ("n_invalid", ctypes.c_uint32), ("reserved", ctypes.c_uint32)]
 
 
+_torch_module = None
+
+
+def _torch():
+    """torch, imported on first use (an import statement per call costs more
+    than the look-up)."""
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
+
+
 def new_stats(n: Optional[int] = None, device="cuda"):
     """bn_frame_stats storage: int32 [STATS_WORDS] (or [n, STATS_WORDS]),
     zeroed.  Words 0..2 are the VALID / BOUNDARY / INVALID counts."""
@@ -57,10 +72,20 @@ def new_stats(n: Optional[int] = None, device="cuda"):
     return torch.zeros(shape, dtype=torch.int32, device=device)
 
 
+def _stats_for(n, pixels, accumulate, device):
+    """Stats for a call that allocates its own: a launch stores every word, so
+    only calls without one (no pixels) or that add to the words need zeros."""
+    if accumulate or pixels == 0:
+        return new_stats(n, device=device)
+    torch = _torch()
+    return torch.empty((STATS_WORDS,) if n is None else (n, STATS_WORDS), dtype=torch.int32,
+                       device=device)
+
+
 def _check_stats(stats, shape, device):
     """A stats tensor the C ABI can write: int32, contiguous, on the depth's
     device, of exactly `shape` (so no write lands past its end)."""
-    import torch
+    torch = _torch()
     if not isinstance(stats, torch.Tensor) or stats.dtype != torch.int32 or \
             tuple(stats.shape) != tuple(shape) or not stats.is_contiguous() or \
             stats.device != device:
@@ -236,15 +261,33 @@ def make_params(alpha: int = 2, mode="rel", tau: float = 4.0, variant: int = 0,
                   FLAG_COUNTS_ACCUMULATE if accumulate_counts else 0, 0)
 
 
+@functools.lru_cache(maxsize=256)
+def _params_of(alpha, m, tau, variant, me, scales, flags):
+    return Params(alpha, m, tau, variant, me, scales, flags, 0)
+
+
+def _params(alpha, mode, tau, variant=0, method="four_pair", scales=0, accumulate_counts=False):
+    """make_params for a call of this module: one structure per set of values,
+    which nobody writes to."""
+    m = MODES[mode] if isinstance(mode, str) else int(mode)
+    me = METHODS[method] if isinstance(method, str) else int(method)
+    return _params_of(int(alpha), m, float(tau), int(variant), me, int(scales),
+                      FLAG_COUNTS_ACCUMULATE if accumulate_counts else 0)
+
+
 def _stream_handle(stream) -> int:
-    import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current device's current stream (torch.cuda.current_stream()
+        # without the Stream object that it makes)
+        torch = _torch()
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check_depth(depth):
-    import torch
+    torch = _torch()
     if not isinstance(depth, torch.Tensor) or not depth.is_cuda:
         raise TypeError("depth must be a CUDA (HIP) torch tensor")
     if depth.dtype != torch.float32 or depth.dim() != 2:
@@ -265,37 +308,35 @@ def estimate_normals(depth, fx: float, fy: float, cx: float, cy: float, alpha: i
     (added to it with accumulate_counts); without one, one is allocated when
     want_stats.  Returns (normals, mask, stats_or_None).
     """
-    import torch
+    torch = _torch()
     _check_depth(depth)
     H, W = depth.shape
     dev = depth.device
+    f32 = torch.float32
     if normals is None:
-        normals = torch.empty((H, W, 3), dtype=torch.float32, device=dev)
+        normals = torch.empty((H, W, 3), dtype=f32, device=dev)
+    elif not (normals.is_contiguous() and normals.shape == (H, W, 3) and normals.dtype == f32):
+        raise ValueError("normals must be a contiguous float32 [H, W, 3] tensor")
     if mask is None:
         mask = torch.empty((H, W), dtype=torch.uint8, device=dev)
-    if stats is None and want_stats:
-        stats = new_stats(device=dev)
-    if not (normals.is_contiguous() and normals.shape == (H, W, 3)
-            and normals.dtype == torch.float32):
-        raise ValueError("normals must be a contiguous float32 [H, W, 3] tensor")
-    if not (mask.is_contiguous() and mask.shape == (H, W) and mask.dtype == torch.uint8):
+    elif not (mask.is_contiguous() and mask.shape == (H, W) and mask.dtype == torch.uint8):
         raise ValueError("mask must be a contiguous uint8 [H, W] tensor")
     if stats is not None:
         _check_stats(stats, (STATS_WORDS,), dev)
-    p = make_params(alpha, mode, tau, variant, method, scales, accumulate_counts)
-    stride = depth.stride(0) if H > 0 else W
+    elif want_stats:
+        stats = _stats_for(None, H * W, accumulate_counts, dev)
+    p = _params(alpha, mode, tau, variant, method, scales, accumulate_counts)
     rc = lib().bn_estimate_normals(
-        ctypes.c_void_p(depth.data_ptr()), H, W, stride, fx, fy, cx, cy, ctypes.byref(p),
-        ctypes.c_void_p(normals.data_ptr()), ctypes.c_void_p(mask.data_ptr()),
-        ctypes.c_void_p(stats.data_ptr() if stats is not None else 0),
-        ctypes.c_void_p(_stream_handle(stream)))
+        depth.data_ptr(), H, W, depth.stride(0) if H > 0 else W, fx, fy, cx, cy, p,
+        normals.data_ptr(), mask.data_ptr(), stats.data_ptr() if stats is not None else None,
+        _stream_handle(stream))
     if rc != BN_OK:
         raise BnError(rc, "bn_estimate_normals")
     return normals, mask, stats
 
 
 def _check_stack(depth):
-    import torch
+    torch = _torch()
     if not isinstance(depth, torch.Tensor) or not depth.is_cuda:
         raise TypeError("depth must be a CUDA (HIP) torch tensor")
     if depth.dtype != torch.float32 or depth.dim() != 3:
@@ -309,7 +350,8 @@ def _intrinsics_array(intrinsics, n: int):
     sequence of n of them."""
     vals = list(intrinsics)
     if len(vals) == 4 and all(isinstance(v, (int, float)) for v in vals):
-        vals = [tuple(vals)] * n
+        one = Intrinsics(*map(float, vals))
+        return (Intrinsics * max(n, 1)).from_buffer_copy(bytes(one) * max(n, 1))
     if len(vals) != n:
         raise ValueError(f"{len(vals)} intrinsics for {n} frames")
     return (Intrinsics * max(n, 1))(*[Intrinsics(*map(float, v)) for v in vals])
@@ -332,31 +374,34 @@ def estimate_normals_stack(depth, intrinsics, alpha: int = 2, mode="rel", tau: f
     cy) for all frames or n of them.  Returns normals [n, H, W, 3], mask
     [n, H, W] and stats [n, STATS_WORDS] (or None); frame k equals
     estimate_normals on depth[k] bit for bit."""
-    import torch
     _check_stack(depth)
+    return _run_stack(depth, _intrinsics_array(intrinsics, depth.shape[0]),
+                      _params(alpha, mode, tau, variant, method, scales, accumulate_counts),
+                      accumulate_counts, normals, mask, stats, want_stats, stream)
+
+
+def _run_stack(depth, arr, p, accumulate_counts=False, normals=None, mask=None, stats=None,
+               want_stats=True, stream=None):
+    torch = _torch()
     n, H, W = depth.shape
     dev = depth.device
-    arr = _intrinsics_array(intrinsics, n)
     if normals is None:
         normals = torch.empty((n, H, W, 3), dtype=torch.float32, device=dev)
+    elif not (normals.is_contiguous() and normals.shape == (n, H, W, 3)
+              and normals.dtype == torch.float32):
+        raise ValueError("normals must be a contiguous float32 [n, H, W, 3] tensor")
     if mask is None:
         mask = torch.empty((n, H, W), dtype=torch.uint8, device=dev)
-    if stats is None and want_stats:
-        stats = new_stats(n, device=dev)
-    if not (normals.is_contiguous() and normals.shape == (n, H, W, 3)
-            and normals.dtype == torch.float32):
-        raise ValueError("normals must be a contiguous float32 [n, H, W, 3] tensor")
-    if not (mask.is_contiguous() and mask.shape == (n, H, W) and mask.dtype == torch.uint8):
+    elif not (mask.is_contiguous() and mask.shape == (n, H, W) and mask.dtype == torch.uint8):
         raise ValueError("mask must be a contiguous uint8 [n, H, W] tensor")
     if stats is not None:
         _check_stats(stats, (n, STATS_WORDS), dev)
-    p = make_params(alpha, mode, tau, variant, method, scales, accumulate_counts)
+    elif want_stats:
+        stats = _stats_for(n, n * H * W, accumulate_counts, dev)
     row, frame = _stack_strides(depth)
     rc = lib().bn_estimate_normals_stack(
-        ctypes.c_void_p(depth.data_ptr()), n, H, W, row, frame, arr, ctypes.byref(p),
-        ctypes.c_void_p(normals.data_ptr()), ctypes.c_void_p(mask.data_ptr()),
-        ctypes.c_void_p(stats.data_ptr() if stats is not None else 0),
-        ctypes.c_void_p(_stream_handle(stream)))
+        depth.data_ptr(), n, H, W, row, frame, arr, p, normals.data_ptr(), mask.data_ptr(),
+        stats.data_ptr() if stats is not None else None, _stream_handle(stream))
     if rc != BN_OK:
         raise BnError(rc, "bn_estimate_normals_stack")
     return normals, mask, stats
@@ -406,11 +451,39 @@ class BatchFrame:
                              "device")
         self.stats = stats
 
+    def _pack(self, buf, at: int) -> None:
+        """The bn_frame of this frame into buf at byte `at` (as _c, without a
+        structure object per frame)."""
+        d = self.depth
+        H, W = d.shape
+        try:
+            _FRAME.pack_into(buf, at, d.data_ptr(), H, W, d.stride(0) if H > 0 else W, self.fx,
+                             self.fy, self.cx, self.cy, self.normals.data_ptr(),
+                             self.mask.data_ptr(),
+                             self.stats.data_ptr() if self.stats is not None else 0)
+        except (OverflowError, struct.error):   # a value beyond binary32 or int32
+            buf[at:at + _FRAME.size] = bytes(self._c())
+
     def _c(self) -> Frame:
         H, W = self.depth.shape
         return Frame(self.depth.data_ptr(), H, W, self.depth.stride(0) if H > 0 else W,
                      self.fx, self.fy, self.cx, self.cy, self.normals.data_ptr(),
                      self.mask.data_ptr(), self.stats.data_ptr() if self.stats is not None else 0)
+
+
+_FRAME = struct.Struct("@QiiqffffQQQ")   # bn_frame
+assert _FRAME.size == ctypes.sizeof(Frame)
+
+
+def _frames_array(frames, least: int = 0):
+    """bn_frame[] of a list of BatchFrames (at least `least` entries long)."""
+    buf = bytearray(_FRAME.size * max(len(frames), least))
+    for k, f in enumerate(frames):
+        if type(f) is BatchFrame:
+            f._pack(buf, k * _FRAME.size)
+        else:
+            buf[k * _FRAME.size:(k + 1) * _FRAME.size] = bytes(f._c())
+    return (Frame * max(len(frames), least)).from_buffer(buf)
 
 
 class BatchPlan:
@@ -420,7 +493,7 @@ class BatchPlan:
                  method="four_pair", scales: int = 0, accumulate_counts: bool = False):
         L = lib()
         self._frames = list(frames)
-        arr = (Frame * len(self._frames))(*[f._c() for f in self._frames])
+        arr = _frames_array(self._frames)
         self.params = make_params(alpha, mode, tau, 0, method, scales, accumulate_counts)
         h = ctypes.c_void_p()
         rc = L.bn_batch_plan_create(arr, len(self._frames), ctypes.byref(self.params),
@@ -435,22 +508,21 @@ class BatchPlan:
 
     def run(self, stream=None) -> None:
         """Replay the plan's graph on `stream`."""
-        rc = lib().bn_batch_run(self._h, ctypes.c_void_p(_stream_handle(stream)))
+        rc = lib().bn_batch_run(self._h, _stream_handle(stream))
         if rc != BN_OK:
             raise BnError(rc, "bn_batch_run")
 
     def launch(self, stream=None) -> None:
         """The same kernels as plain launches (one kernel for lists of at most
         16 frames, two otherwise): less host time per call than a replay."""
-        rc = lib().bn_batch_launch(self._h, ctypes.c_void_p(_stream_handle(stream)))
+        rc = lib().bn_batch_launch(self._h, _stream_handle(stream))
         if rc != BN_OK:
             raise BnError(rc, "bn_batch_launch")
 
     def update(self, frames, stream=None) -> None:
         frames = list(frames)
-        arr = (Frame * len(frames))(*[f._c() for f in frames])
-        rc = lib().bn_batch_plan_update(self._h, arr, len(frames),
-                                        ctypes.c_void_p(_stream_handle(stream)))
+        rc = lib().bn_batch_plan_update(self._h, _frames_array(frames), len(frames),
+                                        _stream_handle(stream))
         if rc != BN_OK:
             raise BnError(rc, "bn_batch_plan_update")
         self._frames = frames
@@ -500,10 +572,9 @@ def estimate_normals_batch_noalloc(frames, alpha: int = 2, mode="rel", tau: floa
     work areas are a fixed device array shared by every call on the GPU:
     calls must not overlap in time)."""
     frames = list(frames)
-    arr = (Frame * max(len(frames), 1))(*[f._c() for f in frames])
-    p = make_params(alpha, mode, tau, 0, method, scales, accumulate_counts)
-    rc = lib().bn_estimate_normals_batch_noalloc(arr, len(frames), ctypes.byref(p),
-                                                 ctypes.c_void_p(_stream_handle(stream)))
+    p = _params(alpha, mode, tau, 0, method, scales, accumulate_counts)
+    rc = lib().bn_estimate_normals_batch_noalloc(_frames_array(frames, 1), len(frames), p,
+                                                 _stream_handle(stream))
     if rc != BN_OK:
         raise BnError(rc, "bn_estimate_normals_batch_noalloc")
 
@@ -550,7 +621,7 @@ def autotune_entries() -> int:
 
 def _check_grad_depth(grad_depth, shape, device):
     """The adjoint writes prod(shape) dense floats: refuse anything else."""
-    import torch
+    torch = _torch()
     if not (isinstance(grad_depth, torch.Tensor) and grad_depth.is_contiguous() and
             tuple(grad_depth.shape) == tuple(shape) and grad_depth.dtype == torch.float32 and
             grad_depth.device == device):
@@ -562,7 +633,7 @@ def normals_vjp(depth, fx, fy, cx, cy, grad_normals, alpha: int = 2, mode="rel",
                 tau: float = 4.0, grad_depth=None, stream=None):
     """d(sum normals . grad_normals)/d depth with every pixel's code held
     fixed (bn_normals_vjp).  Returns grad_depth [H, W] float32."""
-    import torch
+    torch = _torch()
     _check_depth(depth)
     H, W = depth.shape
     g = grad_normals
@@ -572,12 +643,9 @@ def normals_vjp(depth, fx, fy, cx, cy, grad_normals, alpha: int = 2, mode="rel",
     if grad_depth is None:
         grad_depth = torch.empty((H, W), dtype=torch.float32, device=depth.device)
     _check_grad_depth(grad_depth, (H, W), depth.device)
-    p = make_params(alpha, mode, tau, 0)
-    stride = depth.stride(0) if H > 0 else W
-    rc = lib().bn_normals_vjp(ctypes.c_void_p(depth.data_ptr()), H, W, stride, fx, fy, cx, cy,
-                              ctypes.byref(p), ctypes.c_void_p(g.data_ptr()),
-                              ctypes.c_void_p(grad_depth.data_ptr()),
-                              ctypes.c_void_p(_stream_handle(stream)))
+    rc = lib().bn_normals_vjp(depth.data_ptr(), H, W, depth.stride(0) if H > 0 else W, fx, fy, cx,
+                              cy, _params(alpha, mode, tau), g.data_ptr(), grad_depth.data_ptr(),
+                              _stream_handle(stream))
     if rc != BN_OK:
         raise BnError(rc, "bn_normals_vjp")
     return grad_depth
@@ -587,23 +655,23 @@ def normals_vjp_stack(depth, intrinsics, grad_normals, alpha: int = 2, mode="rel
                       tau: float = 4.0, grad_depth=None, stream=None):
     """The adjoint of estimate_normals_stack (bn_normals_vjp_stack): grad
     [n, H, W] from the cotangent [n, H, W, 3], every frame in one launch."""
-    import torch
     _check_stack(depth)
+    return _run_vjp_stack(depth, _intrinsics_array(intrinsics, depth.shape[0]), grad_normals,
+                          _params(alpha, mode, tau), grad_depth, stream)
+
+
+def _run_vjp_stack(depth, arr, g, p, grad_depth=None, stream=None):
+    torch = _torch()
     n, H, W = depth.shape
-    g = grad_normals
     if not (g.is_cuda and g.dtype == torch.float32 and g.shape == (n, H, W, 3)):
         raise ValueError("grad_normals must be a float32 [n, H, W, 3] device tensor")
     g = g.contiguous()
     if grad_depth is None:
         grad_depth = torch.empty((n, H, W), dtype=torch.float32, device=depth.device)
     _check_grad_depth(grad_depth, (n, H, W), depth.device)
-    arr = _intrinsics_array(intrinsics, n)
-    p = make_params(alpha, mode, tau, 0)
     row, frame = _stack_strides(depth)
-    rc = lib().bn_normals_vjp_stack(ctypes.c_void_p(depth.data_ptr()), n, H, W, row, frame, arr,
-                                    ctypes.byref(p), ctypes.c_void_p(g.data_ptr()),
-                                    ctypes.c_void_p(grad_depth.data_ptr()),
-                                    ctypes.c_void_p(_stream_handle(stream)))
+    rc = lib().bn_normals_vjp_stack(depth.data_ptr(), n, H, W, row, frame, arr, p, g.data_ptr(),
+                                    grad_depth.data_ptr(), _stream_handle(stream))
     if rc != BN_OK:
         raise BnError(rc, "bn_normals_vjp_stack")
     return grad_depth
@@ -634,24 +702,27 @@ def _normals_function():
             return gd, None, None, None, None, None, None, None
 
     class StackFunction(torch.autograd.Function):
-        """The same over a stack [n, H, W]: one launch each way."""
+        """The same over a stack [n, H, W]: one launch each way.  `arr`: the
+        bn_intrinsics of the frames, made once for both directions."""
 
         @staticmethod
-        def forward(ctx, depth, intrinsics, alpha, mode, tau):
-            n, m, _ = estimate_normals_stack(depth, intrinsics, alpha, mode, tau,
-                                             want_stats=False)
+        def forward(ctx, depth, arr, alpha, mode, tau):
+            _check_stack(depth)
+            p = _params(alpha, mode, tau)
+            n, m, _ = _run_stack(depth, arr, p, want_stats=False)
             ctx.save_for_backward(depth)
-            ctx.args = (intrinsics, alpha, mode, tau)
+            ctx.args = (arr, p)
             ctx.mark_non_differentiable(m)
             return n, m
 
         @staticmethod
         def backward(ctx, grad_n, grad_m):
             (depth,) = ctx.saved_tensors
-            intrinsics, alpha, mode, tau = ctx.args
+            arr, p = ctx.args
             gd = None
             if ctx.needs_input_grad[0]:
-                gd = normals_vjp_stack(depth, intrinsics, grad_n.float(), alpha, mode, tau)
+                _check_stack(depth)
+                gd = _run_vjp_stack(depth, arr, grad_n.float(), p)
             return gd, None, None, None, None
 
     return NormalsFunction, StackFunction
@@ -677,10 +748,8 @@ def normals_with_grad_stack(depth, intrinsics, alpha: int = 2, mode="rel", tau: 
     global _NormalsFunction, _StackFunction
     if _StackFunction is None:
         _NormalsFunction, _StackFunction = _normals_function()
-    n = depth.shape[0]
-    arr = _intrinsics_array(intrinsics, n)
-    key = tuple((c.fx, c.fy, c.cx, c.cy) for c in arr[:n])
-    return _StackFunction.apply(depth, key, int(alpha), mode, float(tau))
+    arr = _intrinsics_array(intrinsics, depth.shape[0])
+    return _StackFunction.apply(depth, arr, int(alpha), mode, float(tau))
 
 
 COSINE_TILE = 2048               # BN_COSINE_TILE
@@ -691,8 +760,8 @@ def _eager() -> bool:
     """No transform, tracer or mode is active that would have to see the
     tensor operations of a step (vmap, forward-mode, tracing, compilation,
     function or dispatch modes)."""
-    import torch
-    from torch.autograd import forward_ad
+    torch = _torch()
+    forward_ad = torch.autograd.forward_ad
     return (torch._C._functorch.peek_interpreter_stack() is None
             and forward_ad._current_level < 0
             and torch._C._len_torch_dispatch_stack() == 0
@@ -701,7 +770,7 @@ def _eager() -> bool:
 
 
 def _dense(t, dtype, shape, device) -> bool:
-    import torch
+    torch = _torch()
     # (a batched tensor of autograd's own vmap has no storage)
     return (type(t) is torch.Tensor and torch._C._has_storage(t) and t.dtype == dtype
             and t.shape == shape and t.device == device and t.is_contiguous())
@@ -765,7 +834,7 @@ def _cosine_fused(normals, target, mask, target_mask) -> bool:
     [..., 3] and dense uint8 masks [...] on the current GPU, nothing asking
     for a gradient but the normals.  Everything else goes through tensor
     operations."""
-    import torch
+    torch = _torch()
     if not (type(normals) is torch.Tensor and normals.is_cuda and normals.dim() >= 2):
         return False
     dev, shape = normals.device, normals.shape
@@ -781,7 +850,7 @@ def cosine_loss(normals, target, mask, target_mask):
     """mean over pixels valid in both of (1 - normals . target); any leading
     shape (one frame or a stack).  No host synchronisation."""
     global _CosineLoss
-    import torch
+    torch = _torch()
     if _cosine_fused(normals, target, mask, target_mask):
         if _CosineLoss is None:
             _CosineLoss = _cosine_function()
@@ -987,7 +1056,7 @@ def device_to_host(ptr: int, nbytes: int):
 # ---------------------------------------------------------------------------
 
 def _check_normals(n, what="normals"):
-    import torch
+    torch = _torch()
     if not (isinstance(n, torch.Tensor) and n.is_cuda and n.dtype == torch.float32
             and n.dim() == 3 and n.shape[2] == 3 and n.is_contiguous()):
         raise ValueError(f"{what} must be a contiguous CUDA float32 [H, W, 3] tensor")

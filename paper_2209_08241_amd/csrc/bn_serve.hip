@@ -417,6 +417,7 @@ class Server {
     }
 
     int release(uint64_t id) {
+        bool waiting;
         {
             std::lock_guard<std::mutex> g(mu_);
             auto it = all_.find(id);
@@ -426,8 +427,11 @@ class Server {
             if (r->normals) arena_.release(r->slot_off, r->slot_bytes);
             all_.erase(it);
             ++n_released_;
+            waiting = !pending_.empty();
         }
-        cv_.notify_all();
+        // the returned memory matters to requests that wait for admission only
+        // (waking an idle scheduler costs the releasing thread microseconds)
+        if (waiting) cv_.notify_all();
         return BN_OK;
     }
 
