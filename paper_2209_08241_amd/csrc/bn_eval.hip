@@ -282,15 +282,34 @@ __device__ __forceinline__ double adjugate_vec(const double a[6], double b0, dou
     return best;
 }
 
+// The root y in [0, 1] of y^2 (3 + y) = t, t in [0, 4] (clamped).  With s =
+// sqrt(t), y is within 0.1% of s / sqrt(3 + 0.57735 s - 0.0387 s^2), and Newton's
+// steps on y^2 (3 + y) - t double the relative accuracy for every t, also near
+// the double root t = 0: one step in binary32 and two in FP64, no loop.
+__device__ __forceinline__ double cubic_root(double t) {
+    t = t < 1e-30 ? 1e-30 : (t > 4.0 ? 4.0 : t);
+    const float tf = (float)t;
+    const float sf = __builtin_amdgcn_sqrtf(tf);
+    float yf = sf * __builtin_amdgcn_rsqf(
+                        __builtin_fmaf(sf, __builtin_fmaf(sf, -0.0387f, 0.57735f), 3.0f));
+    yf = __builtin_fmaf(-__builtin_fmaf(yf * yf, 3.0f + yf, -tf),
+                        __builtin_amdgcn_rcpf(yf * __builtin_fmaf(3.0f, yf, 6.0f)), yf);
+    double y = (double)yf;
+    const double idh = (double)__builtin_amdgcn_rcpf(yf * __builtin_fmaf(3.0f, yf, 6.0f));
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {  // one slope serves both steps
+        const double h = __builtin_fma(y * y, 3.0 + y, -t);
+        y = __builtin_fma(-h, idh, y);
+    }
+    return y;
+}
+
 // Smallest-eigenvalue eigenvector of the symmetric 3x3 matrix
 // [a0 a1 a2; a1 a3 a4; a2 a4 a5].  With q = tr(A)/3, B = A - q I,
 // p^2 = |B|^2 / 6 and
-// r = det(B) / (2 p^3), lambda = q - p (1 + y) for the root y in [0, 1] of
-// y^2 (3 + y) = t, t = 2 - 2r in [0, 4].  With s = sqrt(t), y is within 0.1% of
-// s / sqrt(3 + 0.57735 s - 0.0387 s^2), and Newton's steps on y^2 (3 + y) - t
-// double the relative accuracy for every t, also near a double root (t = 0):
-// one step in binary32 and two in FP64, no loop.  (The trigonometric closed
-// form costs an FP64 acos, a cos and three divisions.)
+// r = det(B) / (2 p^3), lambda = q - p (1 + y) with y^2 (3 + y) = 2 - 2r
+// (cubic_root; the trigonometric closed form costs an FP64 acos, a cos and
+// three divisions).
 // y is returned: half the gap between the two smallest eigenvalues, over p.
 // False when the vector is not defined.
 __device__ __forceinline__ bool smallest_eigvec(const double a[6], double n[3], double &gap) {
@@ -306,20 +325,7 @@ __device__ __forceinline__ bool smallest_eigvec(const double a[6], double n[3], 
     const double m2 = __builtin_fma(a[1], a[4], -(b3 * a[2]));
     const double det = __builtin_fma(b0, m0, __builtin_fma(a[2], m2, -(a[1] * m1)));
     double t = __builtin_fma(-(det * ip), ip * ip, 2.0);
-    t = t < 1e-30 ? 1e-30 : (t > 4.0 ? 4.0 : t);
-    const float tf = (float)t;
-    const float sf = __builtin_amdgcn_sqrtf(tf);
-    float yf = sf * __builtin_amdgcn_rsqf(
-                        __builtin_fmaf(sf, __builtin_fmaf(sf, -0.0387f, 0.57735f), 3.0f));
-    yf = __builtin_fmaf(-__builtin_fmaf(yf * yf, 3.0f + yf, -tf),
-                        __builtin_amdgcn_rcpf(yf * __builtin_fmaf(3.0f, yf, 6.0f)), yf);
-    double y = (double)yf;
-    const double idh = __builtin_amdgcn_rcp(y * __builtin_fma(3.0, y, 6.0));
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {  // one slope serves both steps
-        const double h = __builtin_fma(y * y, 3.0 + y, -t);
-        y = __builtin_fma(-h, idh, y);
-    }
+    const double y = cubic_root(t);
     gap = y;
     const double best = adjugate_vec(a, b0, b3, b5, -__builtin_fma(p, y, p), n);
     // Where the two smallest eigenvalues lie close (windows across a depth
@@ -342,56 +348,11 @@ __device__ __forceinline__ bool smallest_eigvec(const double a[6], double n[3], 
     return (p2 > 0.0) & (best > 0.0) & (best < (double)INFINITY);
 }
 
-// Smallest-eigenvalue eigenvector of the symmetric 3x3 matrix
-// [a0 a1 a2; a1 a3 a4; a2 a4 a5]: eigenvalue from the trigonometric
-// solution of the characteristic cubic, eigenvector as the longest cross
-// product of two rows of (A - lambda I).  False when it is not defined.
-__device__ __forceinline__ bool smallest_eigvec_trig(const double a[6], double n[3]) {
-    const double q = (a[0] + a[3] + a[5]) / 3.0;
-    const double b0 = a[0] - q, b3 = a[3] - q, b5 = a[5] - q;
-    const double p2 = (b0 * b0 + b3 * b3 + b5 * b5 + 2.0 * (a[1] * a[1] + a[2] * a[2] + a[4] * a[4])) / 6.0;
-    if (!(p2 > 0.0)) return false;
-    const double p = sqrt(p2);
-    const double det = b0 * (b3 * b5 - a[4] * a[4]) - a[1] * (a[1] * b5 - a[4] * a[2]) +
-                       a[2] * (a[1] * a[4] - b3 * a[2]);
-    double r = det / (2.0 * p2 * p);
-    r = r < -1.0 ? -1.0 : (r > 1.0 ? 1.0 : r);
-    const double lam = q + 2.0 * p * cos(acos(r) / 3.0 + kTwoPi / 3.0);
-    const double r0[3] = {a[0] - lam, a[1], a[2]};
-    const double r1[3] = {a[1], a[3] - lam, a[4]};
-    const double r2[3] = {a[2], a[4], a[5] - lam};
-    double c[3][3];
-    c[0][0] = r0[1] * r1[2] - r0[2] * r1[1];
-    c[0][1] = r0[2] * r1[0] - r0[0] * r1[2];
-    c[0][2] = r0[0] * r1[1] - r0[1] * r1[0];
-    c[1][0] = r0[1] * r2[2] - r0[2] * r2[1];
-    c[1][1] = r0[2] * r2[0] - r0[0] * r2[2];
-    c[1][2] = r0[0] * r2[1] - r0[1] * r2[0];
-    c[2][0] = r1[1] * r2[2] - r1[2] * r2[1];
-    c[2][1] = r1[2] * r2[0] - r1[0] * r2[2];
-    c[2][2] = r1[0] * r2[1] - r1[1] * r2[0];
-    int best = 0;
-    double bn = -1.0;
-    for (int k = 0; k < 3; ++k) {
-        const double l = c[k][0] * c[k][0] + c[k][1] * c[k][1] + c[k][2] * c[k][2];
-        if (l > bn) {
-            bn = l;
-            best = k;
-        }
-    }
-    if (!(bn > 0.0) || !isfinite(bn)) return false;
-    const double inv = 1.0 / sqrt(bn);
-    n[0] = c[best][0] * inv;
-    n[1] = c[best][1] * inv;
-    n[2] = c[best][2] * inv;
-    return true;
-}
-
-// The window's scatter matrix from the points' own products and its
-// eigenvector from the trigonometric form, for the few windows whose two
-// smallest eigenvalues agree to kFitDirect of the spread (about one in 10^4,
-// all across depth steps): a vector there is defined to about 1e-16 / y^2
-// only, so it keeps the plain evaluation of the definition, in its order.
+// The window's scatter matrix from the points' own products, for the few
+// windows whose two smallest eigenvalues agree to kFitDirect of the spread
+// (about one in 10^4, all across depth steps): a vector there is defined to
+// about 1e-16 / y^2 only, so these keep the plain evaluation of the
+// definition, up to r, in its order.
 constexpr double kFitDirect = 1e-6;
 
 template <int R>
@@ -430,7 +391,17 @@ __device__ __forceinline__ bool fit_direct(const float *__restrict__ depth, int6
     const double c[3] = {s[0] / N, s[1] / N, s[2] / N};
     const double a[6] = {m[0] - N * c[0] * c[0], m[1] - N * c[0] * c[1], m[2] - N * c[0] * c[2],
                          m[3] - N * c[1] * c[1], m[4] - N * c[1] * c[2], m[5] - N * c[2] * c[2]};
-    if (!smallest_eigvec_trig(a, n)) return false;
+    const double q = (a[0] + a[3] + a[5]) / 3.0;
+    const double b0 = a[0] - q, b3 = a[3] - q, b5 = a[5] - q;
+    const double p2 = (b0 * b0 + b3 * b3 + b5 * b5 +
+                       2.0 * (a[1] * a[1] + a[2] * a[2] + a[4] * a[4])) / 6.0;
+    const double p = sqrt(p2);
+    const double det = b0 * (b3 * b5 - a[4] * a[4]) - a[1] * (a[1] * b5 - a[4] * a[2]) +
+                       a[2] * (a[1] * a[4] - b3 * a[2]);
+    const double r = det / (2.0 * p2 * p);
+    const double gap = cubic_root(2.0 - 2.0 * r);
+    const double best = adjugate_vec(a, b0, b3, b5, -__builtin_fma(p, gap, p), n);
+    if (!(p2 > 0.0 && best > 0.0 && best < (double)INFINITY)) return false;
     if (n[0] * u0 + n[1] * v0 + n[2] > 0.0) {
         n[0] = -n[0];
         n[1] = -n[1];
