@@ -305,13 +305,16 @@ __device__ __forceinline__ void vjp4_band(const FrameArgs &f, const float *__res
             out_store(v, out_buf(gd + (int64_t)y * f.W, 4u * (uint32_t)f.W), 4u * (uint32_t)x0);
             return;
         }
-        // rows that start anywhere: stores through L2, which joins the parts
-        // of a line that neighbouring strips write
-        float *g = gd + (int64_t)y * f.W + x0;
+        // rows that start anywhere: streaming stores through L2, which joins
+        // the parts of a line that neighbouring strips write (four frames of
+        // 1277x719: 18.1 us; plain stores 22.0, device-scope ones 19.9; 16 of
+        // 637x479 24.0, 25.5 and 26.9)
         if (x0 + 4 <= f.W) {
-            *reinterpret_cast<f4u *>(g) = v;
+            out_store<kOutJoin>(v, out_buf(gd + (int64_t)y * f.W, 4u * (uint32_t)f.W),
+                                4u * (uint32_t)x0);
             return;
         }
+        float *g = gd + (int64_t)y * f.W + x0;
         g[0] = v.x;
         if (x0 + 1 < f.W) g[1] = v.y;
         if (x0 + 2 < f.W) g[2] = v.z;
@@ -439,8 +442,7 @@ static bool aligned16(const void *p) { return ((uintptr_t)p % 16) == 0; }
 // them to hide it (scalar against vector: alpha 2, 320x240 3.9 / 6.2 us,
 // 640x480 5.3 / 6.4, two of them 8.4 / 7.4, 1280x720 10.0 / 8.8; alpha 4,
 // 640x480 6.7 / 10.8, two 10.6 / 11.7, 1280x720 12.9 / 11.9).  As scalar
-// tiles, ragged frames took: four of 1277x719, alpha 1..4, 26.7, 29.0, 36.7 and
-// 38.4 us; now 21.3, 21.3, 22.3 and 23.1.
+// tiles, ragged frames took: four of 1277x719, alpha 2, 29.0 us, now 18.1.
 static bool vjp4_serves(int32_t n, int32_t H, int32_t W, int alpha) {
     return alpha <= 4 && W >= 4 &&
            (int64_t)n * H * W > (alpha <= 2 ? (int64_t)3 << 17 : (int64_t)3 << 18);

@@ -461,6 +461,9 @@ __device__ __forceinline__ PixelOut eval_pixel_multiscale(bool inside, const flo
 // lives in scalar registers.
 // ---------------------------------------------------------------------------
 constexpr int kOutPolicy = 2 | 16;          // nt | sc1
+// Streaming, but through L2: for runs of stores that start and end within a
+// line, whose parts L2 joins before they go to memory.
+constexpr int kOutJoin = 2;                 // nt
 constexpr int kRsrcFormat = 0x00020000;     // word 3: 32-bit data format, no swizzle
 
 struct OutBuf {
@@ -476,8 +479,9 @@ __device__ __forceinline__ uint32_t wave_id() {
 __device__ __forceinline__ OutBuf out_buf(void *base, uint32_t bytes) {
     return OutBuf{__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, kRsrcFormat)};
 }
+template <int POLICY = kOutPolicy>
 __device__ __forceinline__ void out_store(f4 v, const OutBuf &b, uint32_t off) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, b.r, off, 0, kOutPolicy);
+    __builtin_amdgcn_raw_buffer_store_b128(v, b.r, off, 0, POLICY);
 }
 __device__ __forceinline__ void out_store(uint32_t v, const OutBuf &b, uint32_t off) {
     __builtin_amdgcn_raw_buffer_store_b32(v, b.r, off, 0, kOutPolicy);
