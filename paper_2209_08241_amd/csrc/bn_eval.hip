@@ -43,12 +43,12 @@ __device__ __forceinline__ double atan2_finite(double y, double x) {
         0x1.5a4830043ba61p-6,
     };
     const double ay = __builtin_fabs(y), ax = __builtin_fabs(x);
-    const bool steep = ay > ax;
-    const double mx = steep ? ay : ax, mn = steep ? ax : ay;
-    const bool big = mn > 0.41421356237309503 * mx;
-    const double num = big ? mn - mx : mn;
-    double den = big ? mn + mx : mx;
-    den = __builtin_fmax(den, 1e-300);  // 0 / 0: the zero vector
+    const bool steep = ay > ax, left = __builtin_signbit(x);
+    const double mx = __builtin_fmax(ay, ax), mn = __builtin_fmin(ay, ax);
+    // a 0 or 1 in FP64 is one select (of the high word), a selected value two
+    const double big = mn > 0.41421356237309503 * mx ? 1.0 : 0.0;
+    const double num = __builtin_fma(-big, mx, mn);
+    const double den = __builtin_fmax(__builtin_fma(big, mn, mx), 1e-300);  // (the zero vector)
     double r = __builtin_amdgcn_rcp(den);
     r = __builtin_fma(r, __builtin_fma(-den, r, 1.0), r);
     double t = num * r;
@@ -58,9 +58,10 @@ __device__ __forceinline__ double atan2_finite(double y, double x) {
 #pragma unroll
     for (int k = 8; k >= 0; --k) q = __builtin_fma(q, u, kQ[k]);
     double a = __builtin_fma(t * u, q, t);
-    a = big ? a + 0.25 * kPi : a;
-    a = steep ? 0.5 * kPi - a : a;
-    a = __builtin_signbit(x) ? kPi - a : a;
+    a = __builtin_fma(big, 0.25 * kPi, a);
+    // a, pi/2 - a, pi - a or pi/2 + a
+    a = steep != left ? -a : a;
+    a += steep ? 0.5 * kPi : (left ? kPi : 0.0);
     return __builtin_copysign(a, y);
 }
 
@@ -125,7 +126,7 @@ __device__ __forceinline__ Angles angles_of(float x, float y, float z) {
 // One pixel per thread: FP64 arithmetic and traffic (12 bytes in, 8 out per
 // pixel) about balance, and overlap best with many wavefronts in turn (four
 // pixels per thread, with 16-byte loads and stores, 13.9 against 12.5 us).
-// 1920x1080 14.4 -> 11.2 us, 640x480 4.05 -> 3.6 (with the library's atan2 and
+// 1920x1080 14.4 -> 10.4 us, 640x480 4.05 -> 3.5 (with the library's atan2 and
 // plain stores before).
 __global__ __launch_bounds__(256) void k_angles(const float *__restrict__ normals, uint32_t npix,
                                                 float *__restrict__ theta,
@@ -157,12 +158,15 @@ __device__ __forceinline__ void block_sum3(double &a, double &b, double &c) {
         s[w][2] = c;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < TB / 64; ++k) {
-            a += s[k][0];
-            b += s[k][1];
-            c += s[k][2];
-        }
+    // lane j sums the wavefronts' totals of quantity j
+    if (threadIdx.x < 64u) {
+        const uint32_t j = min(threadIdx.x, 2u);
+        double v = s[0][j];
+#pragma unroll
+        for (int k = 1; k < TB / 64; ++k) v += s[k][j];
+        a = __shfl(v, 0);
+        b = __shfl(v, 1);
+        c = __shfl(v, 2);
     }
 }
 
@@ -207,7 +211,7 @@ __device__ __forceinline__ AngleDiff angle_diff(float ax, float ay, float az, fl
 // Partial sums of (dtheta^2, dphi^2, count) over a grid-stride share of the
 // pixels, one triple per workgroup (in three planes of kMseBlocks).  A null
 // mask counts as all VALID.  1920x1080, both
-// kernels: 30.6 us with four arc tangents of the library per pixel, now 22.6.
+// kernels: 30.6 us with four arc tangents of the library per pixel, now 21.7.
 __global__ __launch_bounds__(256) void k_mse_partial(const float *__restrict__ na,
                                                      const uint8_t *__restrict__ ma,
                                                      const float *__restrict__ nb,
