@@ -291,7 +291,7 @@ __device__ __forceinline__ double adjugate_vec(const double a[6], double b0, dou
 // steps on y^2 (3 + y) - t double the relative accuracy for every t, also near
 // the double root t = 0: one step in binary32 and two in FP64, no loop.
 __device__ __forceinline__ double cubic_root(double t) {
-    t = t < 1e-30 ? 1e-30 : (t > 4.0 ? 4.0 : t);
+    t = __builtin_fmin(__builtin_fmax(t, 1e-30), 4.0);
     const float tf = (float)t;
     const float sf = __builtin_amdgcn_sqrtf(tf);
     float yf = sf * __builtin_amdgcn_rsqf(
@@ -315,8 +315,9 @@ __device__ __forceinline__ double cubic_root(double t) {
 // (cubic_root; the trigonometric closed form costs an FP64 acos, a cos and
 // three divisions).
 // y is returned: half the gap between the two smallest eigenvalues, over p.
-// False when the vector is not defined.
-__device__ __forceinline__ bool smallest_eigvec(const double a[6], double n[3], double &gap) {
+// False when the vector is not defined, or wanted is false.
+__device__ __forceinline__ bool smallest_eigvec(const double a[6], bool wanted, double n[3],
+                                                double &gap) {
     const double q = (a[0] + a[3] + a[5]) * (1.0 / 3.0);
     const double b0 = a[0] - q, b3 = a[3] - q, b5 = a[5] - q;
     const double off = __builtin_fma(a[1], a[1], __builtin_fma(a[2], a[2], a[4] * a[4]));
@@ -337,7 +338,10 @@ __device__ __forceinline__ bool smallest_eigvec(const double a[6], double n[3], 
     // gap; the vector's Rayleigh quotient does not.  (Vectors of 640x480
     // scenes: mean error 4e-9..3e-8 without this step, like the trigonometric
     // form's, 2e-13 with it.)
-    if (y < 1e-4) {
+    // Windows with a missing depth, which no one wants, mostly look like that
+    // too: with them nearly every wavefront took the branch (1080p 32.9 us, now
+    // 29.5; R = 3 at 1280x720 18.8, now 16.3).
+    if (wanted & (y < 1e-4)) {
         const double g0 = __builtin_fma(b0, n[0], __builtin_fma(a[1], n[1], a[2] * n[2]));
         const double g1 = __builtin_fma(a[1], n[0], __builtin_fma(b3, n[1], a[4] * n[2]));
         const double g2 = __builtin_fma(a[2], n[0], __builtin_fma(a[4], n[1], b5 * n[2]));
@@ -349,7 +353,7 @@ __device__ __forceinline__ bool smallest_eigvec(const double a[6], double n[3], 
             n[2] = v[2];
         }
     }
-    return (p2 > 0.0) & (best > 0.0) & (best < (double)INFINITY);
+    return wanted & (p2 > 0.0) & (best > 0.0) & (best < (double)INFINITY);
 }
 
 // The window's scatter matrix from the points' own products, for the few
@@ -551,7 +555,7 @@ __device__ __forceinline__ float wave_min(float v) {
 // and TY rows: TY = 4 shares the loads and the columns' conversions over four
 // rows, TY = 1 makes four times the wavefronts of smaller frames.  About 290
 // VALU instructions per output at R = 2 (FP64 ones issue at 30 T lane-op/s
-// here): 1080p 84 -> 34 us, 640x480 15.7 -> 7.3 us, R = 3 at 1280x720 61 -> 18
+// here): 1080p 84 -> 29 us, 640x480 15.7 -> 6.7 us, R = 3 at 1280x720 61 -> 16
 // us against 25-tap sums per pixel with the trigonometric eigenvalue.  Row
 // sums kept in a register ring down the rows (no LDS) took 27 us without the
 // two branches on close eigenvalues, but spilled with them (41 us).
@@ -616,7 +620,7 @@ __global__ __launch_bounds__(256, 4) void k_plane_fit(const float *__restrict__ 
         fit_scatter<R>(fit_col<R>(c + k - 2 * R, q + k - 2 * R), s_fit[w], lane, D, u0, v0, ifx,
                        ify, a);
         const bool in = ((full >> lane) & 1u) & x_in;
-        const bool ok = smallest_eigvec(a, n, gap) & in;
+        const bool ok = smallest_eigvec(a, in, n, gap);
         close |= (uint32_t)(in & (gap < kFitDirect)) << (k - 2 * R);
         const bool away = __builtin_fma(n[0], u0, __builtin_fma(n[1], v0, n[2])) > 0.0;
         const int64_t i0 = (int64_t)y * W + xb;
@@ -670,8 +674,8 @@ typedef void (*FitFn)(const float *, int32_t, int32_t, int64_t, double, double, 
 
 // Rows per wavefront: 4, or 1 for frames below kFitSmall pixels, whose
 // wavefronts of 4 rows would not fill the chip once (TY 4 against TY 1:
-// 320x240 6.8 / 4.4 us, 640x480 9.0 / 7.3, 1000x600 11.8 / 10.8, 1280x720 14.8
-// / 15.2, 1440x900 20.5 / 20.6, 1920x1080 34.4 / 36.9).
+// 320x240 6.3 / 4.6 us, 640x480 8.2 / 6.7, 1000x600 10.6 / 9.7, 1280x720 12.9
+// / 13.5, 1440x900 17.7 / 18.2, 1920x1080 29.3 / 32.2).
 constexpr int64_t kFitSmall = 3 << 18;
 
 FitFn fit_kernel(int r, bool small) {
