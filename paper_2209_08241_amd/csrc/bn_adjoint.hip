@@ -375,11 +375,13 @@ __global__ __launch_bounds__(64 * NW) void k_vjp4_stack(const StackArgs s) {
 // (Measured with six buffer sets: 8-row bands for a = 2 took 14.9 against
 // 11.6 us on a 1920x1080 frame, 35.9 against 31.2 us on 64 frames of
 // 320x240, and the same on 16 frames of 640x480 or 4 of 1920x1080.)
-// Wavefronts per workgroup: 8 (a band of 8 RB rows shares its 2a outer rows
-// among more rows) when that still gives kVjpWide workgroups, else 4
-// (measured: 16 x 640x480 25.4 against 26.1 us, 4 x 1920x1080 39.5
-// against 41.2; one 1920x1080 frame, 306 workgroups of 8, 13.4 against
-// 12.4 us).
+// Wavefronts per workgroup: a <= 2 (5 wavefronts per SIMD): 8 (a band of 8 RB
+// rows shares its 2a outer rows among more rows) when that still gives kVjpWide
+// workgroups, else 4 (measured: 16 x 640x480 22.9 against 24.0 us, 4 x
+// 1920x1080 38.7 against 39.9; one 1920x1080 frame, 306 workgroups of 8, 13.4
+// against 12.4 us).  a = 3, 4 (3 per SIMD: a compute unit holds one workgroup of
+// 8 or three of 4): 4 (24 x 640x480 43.1 us with 8, 38.8 with 4; 4 x 1920x1080
+// 46.3 / 45.0; one 4096x3072 61.9 / 61.3; 6 x 1917x1079 64.4 / 65.0).
 constexpr uint64_t kVjpWide = 512;
 
 struct Vjp4Shape {
@@ -392,7 +394,7 @@ static Vjp4Shape vjp4_shape(int32_t H, int32_t W, int32_t n, int alpha) {
     s.strips = (uint32_t)(((W + 3) / 4 + kVjpGroups - 1) / kVjpGroups);
     s.rb = alpha <= 2 ? 4 : 8;
     const uint64_t wide = (uint64_t)s.strips * (uint64_t)((H + 8 * s.rb - 1) / (8 * s.rb)) * n;
-    s.nw = wide >= kVjpWide ? 8 : 4;
+    s.nw = alpha <= 2 && wide >= kVjpWide ? 8 : 4;
     s.bands = (uint32_t)((H + s.nw * s.rb - 1) / (s.nw * s.rb));
     return s;
 }
@@ -400,13 +402,14 @@ static Vjp4Shape vjp4_shape(int32_t H, int32_t W, int32_t n, int alpha) {
 typedef void (*Vjp4Fn)(FrameArgs, const float *, float *, uint32_t);
 typedef void (*Vjp4StackFn)(const StackArgs);
 
+// (a = 3, 4: workgroups of 4 wavefronts only)
 template <int NW, bool RAGGED>
 static Vjp4Fn vjp4_kernel_w(int a) {
     switch (a) {
         case 1: return k_vjp4<1, 4, NW, RAGGED>;
         case 2: return k_vjp4<2, 4, NW, RAGGED>;
-        case 3: return k_vjp4<3, 8, NW, RAGGED>;
-        case 4: return k_vjp4<4, 8, NW, RAGGED>;
+        case 3: return k_vjp4<3, 8, 4, RAGGED>;
+        case 4: return k_vjp4<4, 8, 4, RAGGED>;
     }
     return nullptr;
 }
@@ -416,8 +419,8 @@ static Vjp4StackFn vjp4_stack_kernel_w(int a) {
     switch (a) {
         case 1: return k_vjp4_stack<1, 4, NW, RAGGED>;
         case 2: return k_vjp4_stack<2, 4, NW, RAGGED>;
-        case 3: return k_vjp4_stack<3, 8, NW, RAGGED>;
-        case 4: return k_vjp4_stack<4, 8, NW, RAGGED>;
+        case 3: return k_vjp4_stack<3, 8, 4, RAGGED>;
+        case 4: return k_vjp4_stack<4, 8, 4, RAGGED>;
     }
     return nullptr;
 }
