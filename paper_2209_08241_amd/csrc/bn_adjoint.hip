@@ -370,18 +370,23 @@ __global__ __launch_bounds__(64 * NW) void k_vjp4_stack(const StackArgs s) {
                          s.gd + (int64_t)k * npix, t % s.tiles_x, t / s.tiles_x);
 }
 
-// Rows per wavefront: the fewest that the band edges allow (RB >= 2a), so
-// that the grid holds the most workgroups: 4 for a <= 2, 8 for a = 3, 4.
-// (Measured with six buffer sets: 8-row bands for a = 2 took 14.9 against
-// 11.6 us on a 1920x1080 frame, 35.9 against 31.2 us on 64 frames of
-// 320x240, and the same on 16 frames of 640x480 or 4 of 1920x1080.)
-// Wavefronts per workgroup: a <= 2 (5 wavefronts per SIMD): 8 (a band of 8 RB
-// rows shares its 2a outer rows among more rows) when that still gives kVjpWide
-// workgroups, else 4 (measured: 16 x 640x480 22.9 against 24.0 us, 4 x
-// 1920x1080 38.7 against 39.9; one 1920x1080 frame, 306 workgroups of 8, 13.4
-// against 12.4 us).  a = 3, 4 (3 per SIMD: a compute unit holds one workgroup of
-// 8 or three of 4): 4 (24 x 640x480 43.1 us with 8, 38.8 with 4; 4 x 1920x1080
-// 46.3 / 45.0; one 4096x3072 61.9 / 61.3; 6 x 1917x1079 64.4 / 65.0).
+// Rows per wavefront: the fewest that the band edges allow (RB >= 2a), so that
+// the grid holds the most workgroups and a lane the fewest registers: 4 for a
+// <= 2, 6 and 8 for a = 3, 4.  (Measured with six buffer sets: 8-row bands for
+// a = 2 took 14.9 against 11.6 us on a 1920x1080 frame, 35.9 against 31.2 us on
+// 64 frames of 320x240, and the same on 16 frames of 640x480 or 4 of 1920x1080;
+// for a = 3, 135 against 112 VGPRs, 3 wavefronts per SIMD against 4: one
+// 1280x720 frame 12.1 / 10.2, one 1920x1080 14.7 / 12.3, four 45.2 / 42.8, one
+// 4096x3072 62.3 / 57.1, four of 1277x719 19.8 / 17.0; two of 1920x1080 20.7 /
+// 21.5.)
+// Wavefronts per workgroup: 8 (a band of 8 RB rows shares its 2a outer rows
+// among more rows) when that still gives kVjpWide workgroups, else 4
+// (measured: 16 x 640x480 22.9 against 24.0 us, 4 x 1920x1080 38.7 against
+// 39.9; one 1920x1080 frame, 306 workgroups of 8, 13.4 against 12.4; a = 3: 24
+// x 640x480 34.2 / 37.6, one 4096x3072 57.1 / 60.5, 4 x 1920x1080 42.8 / 41.1).
+// a = 4 (3 wavefronts per SIMD: a compute unit holds one workgroup of 8 or
+// three of 4): 4 (24 x 637x479 44.9 us with 8, 39.9 with 4; 8 x 1280x720 42.9 /
+// 40.0; one 4096x3072 61.9 / 61.3).
 constexpr uint64_t kVjpWide = 512;
 
 struct Vjp4Shape {
@@ -392,9 +397,9 @@ struct Vjp4Shape {
 static Vjp4Shape vjp4_shape(int32_t H, int32_t W, int32_t n, int alpha) {
     Vjp4Shape s;
     s.strips = (uint32_t)(((W + 3) / 4 + kVjpGroups - 1) / kVjpGroups);
-    s.rb = alpha <= 2 ? 4 : 8;
+    s.rb = alpha <= 2 ? 4 : 2 * alpha;
     const uint64_t wide = (uint64_t)s.strips * (uint64_t)((H + 8 * s.rb - 1) / (8 * s.rb)) * n;
-    s.nw = alpha <= 2 && wide >= kVjpWide ? 8 : 4;
+    s.nw = alpha <= 3 && wide >= kVjpWide ? 8 : 4;
     s.bands = (uint32_t)((H + s.nw * s.rb - 1) / (s.nw * s.rb));
     return s;
 }
@@ -402,13 +407,13 @@ static Vjp4Shape vjp4_shape(int32_t H, int32_t W, int32_t n, int alpha) {
 typedef void (*Vjp4Fn)(FrameArgs, const float *, float *, uint32_t);
 typedef void (*Vjp4StackFn)(const StackArgs);
 
-// (a = 3, 4: workgroups of 4 wavefronts only)
+// (a = 4: workgroups of 4 wavefronts only)
 template <int NW, bool RAGGED>
 static Vjp4Fn vjp4_kernel_w(int a) {
     switch (a) {
         case 1: return k_vjp4<1, 4, NW, RAGGED>;
         case 2: return k_vjp4<2, 4, NW, RAGGED>;
-        case 3: return k_vjp4<3, 8, 4, RAGGED>;
+        case 3: return k_vjp4<3, 6, NW, RAGGED>;
         case 4: return k_vjp4<4, 8, 4, RAGGED>;
     }
     return nullptr;
@@ -419,7 +424,7 @@ static Vjp4StackFn vjp4_stack_kernel_w(int a) {
     switch (a) {
         case 1: return k_vjp4_stack<1, 4, NW, RAGGED>;
         case 2: return k_vjp4_stack<2, 4, NW, RAGGED>;
-        case 3: return k_vjp4_stack<3, 8, 4, RAGGED>;
+        case 3: return k_vjp4_stack<3, 6, NW, RAGGED>;
         case 4: return k_vjp4_stack<4, 8, 4, RAGGED>;
     }
     return nullptr;

@@ -8,10 +8,10 @@ import paper_2209_08241_amd as bn
 pytestmark = pytest.mark.gpu
 
 
-# 320x240 is 2 strips of 8 bands of 8 wavefronts: 512 workgroups from 32 frames
-# on; alpha 3 and 4 always take 4 wavefronts
+# 320x240 is 2 strips of 8 (alpha 3: 5) bands of 8 wavefronts: 512 workgroups
+# from 32 (52) frames on; alpha 4 always takes 4 wavefronts
 @pytest.mark.parametrize("alpha", [1, 2, 3, 4])
-@pytest.mark.parametrize("n", [31, 32, 33, 42, 43])
+@pytest.mark.parametrize("n", [31, 32, 43, 51, 52])
 @pytest.mark.parametrize("W", [320, 319])
 def test_stacks_equal_single_frames(n, W, alpha):
     import torch
