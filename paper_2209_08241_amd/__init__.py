@@ -771,9 +771,12 @@ def _eager() -> bool:
 
 def _dense(t, dtype, shape, device) -> bool:
     torch = _torch()
-    # (a batched tensor of autograd's own vmap has no storage)
+    # (a batched tensor of autograd's own vmap has no storage; the memory of a
+    # view with the negative bit, as the imaginary part of a conjugate, holds
+    # the opposite sign)
     return (type(t) is torch.Tensor and torch._C._has_storage(t) and t.dtype == dtype
-            and t.shape == shape and t.device == device and t.is_contiguous())
+            and t.shape == shape and t.device == device and t.is_contiguous()
+            and not t.is_neg())
 
 
 def _cosine_function():
