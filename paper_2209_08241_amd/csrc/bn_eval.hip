@@ -195,7 +195,9 @@ __device__ __forceinline__ AngleDiff angle_diff(float ax, float ay, float az, fl
     const bool axis_a = (ax == 0.0f) & (ay == 0.0f), axis_b = (bx == 0.0f) & (by == 0.0f);
     const double za = axis_a & (az == 0.0f) ? (double)__builtin_copysignf(1.0f, az) : (double)az;
     const double zb = axis_b & (bz == 0.0f) ? (double)__builtin_copysignf(1.0f, bz) : (double)bz;
-    d.theta = atan2_finite(__builtin_fma(ra, zb, -(rb * za)), __builtin_fma(za, zb, ra * rb));
+    // two rounded products: exactly 0 for equal vectors (lengths are inexact, so
+    // a fused one would leave the other's rounding)
+    d.theta = atan2_finite(ra * zb - rb * za, __builtin_fma(za, zb, ra * rb));
     const double xa = axis_a ? (double)__builtin_copysignf(1.0f, ax) : (double)ax;
     const double xb = axis_b ? (double)__builtin_copysignf(1.0f, bx) : (double)bx;
     const double ya = ay, yb = by;
