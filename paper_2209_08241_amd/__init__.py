@@ -761,12 +761,13 @@ def _eager() -> bool:
     tensor operations of a step (vmap, forward-mode, tracing, compilation,
     function or dispatch modes)."""
     torch = _torch()
+    if torch.compiler.is_compiling() or torch.jit.is_tracing():
+        return False
     forward_ad = torch.autograd.forward_ad
     return (torch._C._functorch.peek_interpreter_stack() is None
             and forward_ad._current_level < 0
             and torch._C._len_torch_dispatch_stack() == 0
-            and torch._C._len_torch_function_stack() == 0
-            and not torch.jit.is_tracing() and not torch.compiler.is_compiling())
+            and torch._C._len_torch_function_stack() == 0)
 
 
 def _dense(t, dtype, shape, device) -> bool:
@@ -838,7 +839,9 @@ def _cosine_fused(normals, target, mask, target_mask) -> bool:
     for a gradient but the normals.  Everything else goes through tensor
     operations."""
     torch = _torch()
-    if not (type(normals) is torch.Tensor and normals.is_cuda and normals.dim() >= 2):
+    # (_eager before what a tracer cannot take, as _dense)
+    if not (type(normals) is torch.Tensor and normals.is_cuda and normals.dim() >= 2
+            and _eager()):
         return False
     dev, shape = normals.device, normals.shape
     return (shape[-1] == 3 and 0 < normals.numel() <= 3 * COSINE_MAX_PIXELS
@@ -846,7 +849,7 @@ def _cosine_fused(normals, target, mask, target_mask) -> bool:
             and _dense(target, torch.float32, shape, dev) and not target.requires_grad
             and _dense(mask, torch.uint8, shape[:-1], dev)
             and _dense(target_mask, torch.uint8, shape[:-1], dev)
-            and dev.index == torch.cuda.current_device() and _eager())
+            and dev.index == torch.cuda.current_device())
 
 
 def cosine_loss(normals, target, mask, target_mask):
