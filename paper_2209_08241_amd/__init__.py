@@ -282,7 +282,10 @@ def _stream_handle(stream) -> int:
         torch = _torch()
         if not torch.cuda.is_initialized():
             torch.cuda.init()
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:   # a torch without these internal names
+            stream = torch.cuda.current_stream()
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -763,11 +766,13 @@ def _eager() -> bool:
     torch = _torch()
     if torch.compiler.is_compiling() or torch.jit.is_tracing():
         return False
-    forward_ad = torch.autograd.forward_ad
-    return (torch._C._functorch.peek_interpreter_stack() is None
-            and forward_ad._current_level < 0
-            and torch._C._len_torch_dispatch_stack() == 0
-            and torch._C._len_torch_function_stack() == 0)
+    try:
+        return (torch._C._functorch.peek_interpreter_stack() is None
+                and torch.autograd.forward_ad._current_level < 0
+                and torch._C._len_torch_dispatch_stack() == 0
+                and torch._C._len_torch_function_stack() == 0)
+    except AttributeError:   # a torch without these internal names: not known
+        return False
 
 
 def _dense(t, dtype, shape, device) -> bool:
@@ -775,9 +780,12 @@ def _dense(t, dtype, shape, device) -> bool:
     # (a batched tensor of autograd's own vmap has no storage; the memory of a
     # view with the negative bit, as the imaginary part of a conjugate, holds
     # the opposite sign)
-    return (type(t) is torch.Tensor and torch._C._has_storage(t) and t.dtype == dtype
-            and t.shape == shape and t.device == device and t.is_contiguous()
-            and not t.is_neg())
+    try:
+        return (type(t) is torch.Tensor and torch._C._has_storage(t) and t.dtype == dtype
+                and t.shape == shape and t.device == device and t.is_contiguous()
+                and not t.is_neg())
+    except AttributeError:   # a torch without this internal name: not known
+        return False
 
 
 def _cosine_function():
