@@ -650,7 +650,9 @@ int bn_batch_plan_create(const bn_frame *frames_host, int32_t n_frames, const bn
         free_plan(pl);
         return BN_ERR_DEVICE;
     }
-    rc = alloc_buffers(pl, tiles > 0 ? tiles : 1);
+    // tables for the list in any layout (`units`, never fewer than its tiles),
+    // so that later lists of no more pixels fit whatever their frames' layout
+    rc = alloc_buffers(pl, units > 0 ? units : 1);
     if (rc == BN_OK) rc = build_table(frames_host, n_frames, params, pl->capacity, pl->grid,
                                       pl->work, &pl->count_chunks, &pl->has_flat,
                                       pl->staging[0]);
@@ -703,7 +705,7 @@ int bn_batch_plan_update(bn_batch_plan *plan, const bn_frame *frames_host, int32
         // failed allocation leaves the plan as it was
         bn_batch_plan fresh;
         fresh.capacity = plan->capacity;
-        rc = alloc_buffers(&fresh, tiles + tiles / 4);
+        rc = alloc_buffers(&fresh, units + units / 4);
         if (rc != BN_OK) {
             free_buffers(&fresh);
             return rc;

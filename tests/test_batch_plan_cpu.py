@@ -1,0 +1,33 @@
+"""Host side of batch plans on a HIP runtime without a GPU: what a plan's calls
+allocate, instantiate and launch."""
+import os
+
+import pytest
+
+import fake_hip
+
+pytestmark = pytest.mark.skipif(not os.path.exists("/opt/rocm/include/hip/hip_runtime_api.h"),
+                                reason="HIP headers not available")
+
+
+@pytest.fixture(scope="module")
+def so(tmp_path_factory):
+    return fake_hip.build(tmp_path_factory.mktemp("fakehip"))
+
+
+def test_updates_within_a_plans_size_allocate_nothing(so):
+    """A plan made of odd-sized frames holds the tiles of as many pixels in any
+    layout: an update to such a list neither allocates nor waits."""
+    fake_hip.run(so, r"""
+h = create([(479, 637)] * 20)
+log()
+for shapes in ([(480, 640)] * 19, [(480, 636)] * 20, [(720, 1280)] * 20, [(479, 637)] * 20):
+    assert update(h, shapes) == 0
+    assert "alloc" not in log(), shapes
+# normals and codes that start apart: scalar tiles
+fr = frames([(479, 637)] * 20)
+for f in fr:
+    f.mask += 1
+assert L.bn_batch_plan_update(h, fr, 20, None) == 0
+assert "alloc" not in log()
+""")
