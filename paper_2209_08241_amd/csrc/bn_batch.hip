@@ -480,8 +480,16 @@ struct BatchArgs {
     dim3 count_grid(const bn_batch_plan *pl) const { return dim3(nframes ? nframes : 1u, pl->count_chunks); }
 };
 
+void drop_graph(hipGraph_t &graph, hipGraphExec_t &exec) {
+    if (exec) (void)hipGraphExecDestroy(exec);
+    if (graph) (void)hipGraphDestroy(graph);
+    exec = nullptr;
+    graph = nullptr;
+}
+
 // Kernel node parameters (buffer pointers, header values, grids) into the
-// graph, or a fresh graph [tile kernel] -> [count sums] when none exists.
+// graph, or a fresh graph [tile kernel] -> [count sums] when none exists.  A
+// graph that cannot be made leaves none, and the next run tries again.
 int refresh_node(bn_batch_plan *pl) {
     BatchArgs a(pl);
     bn_batch_plan::TableGraph &g = pl->graphs[pl->has_flat];
@@ -489,18 +497,19 @@ int refresh_node(bn_batch_plan *pl) {
         kernel_params(reinterpret_cast<void *>(pl->fns[pl->has_flat]), pl->grid, a.main);
     hipKernelNodeParams cp = kernel_params(reinterpret_cast<void *>(k_batch_counts),
                                            a.count_grid(pl), a.counts);
-    g.stale = false;
     if (!g.exec) {
         if (hipGraphCreate(&g.graph, 0) != hipSuccess ||
             hipGraphAddKernelNode(&g.node, g.graph, nullptr, 0, &kp) != hipSuccess ||
             hipGraphAddKernelNode(&g.count_node, g.graph, &g.node, 1, &cp) != hipSuccess ||
-            hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0) != hipSuccess)
+            hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0) != hipSuccess) {
+            drop_graph(g.graph, g.exec);
             return BN_ERR_DEVICE;
-        return BN_OK;
-    }
-    if (hipGraphExecKernelNodeSetParams(g.exec, g.node, &kp) != hipSuccess ||
-        hipGraphExecKernelNodeSetParams(g.exec, g.count_node, &cp) != hipSuccess)
+        }
+    } else if (hipGraphExecKernelNodeSetParams(g.exec, g.node, &kp) != hipSuccess ||
+               hipGraphExecKernelNodeSetParams(g.exec, g.count_node, &cp) != hipSuccess) {
         return BN_ERR_DEVICE;
+    }
+    g.stale = false;
     return BN_OK;
 }
 
@@ -535,12 +544,8 @@ void free_plan(bn_batch_plan *pl) {
             (void)hipEventDestroy(pl->staged[k]);
         }
     }
-    for (auto &g : pl->graphs) {
-        if (g.exec) (void)hipGraphExecDestroy(g.exec);
-        if (g.graph) (void)hipGraphDestroy(g.graph);
-    }
-    if (pl->sexec) (void)hipGraphExecDestroy(pl->sexec);
-    if (pl->sgraph) (void)hipGraphDestroy(pl->sgraph);
+    for (auto &g : pl->graphs) drop_graph(g.graph, g.exec);
+    drop_graph(pl->sgraph, pl->sexec);
     if (pl->work) (void)hipFree(pl->work);
     free_buffers(pl);
     delete pl;
@@ -552,17 +557,18 @@ int refresh_small_node(bn_batch_plan *pl) {
     void *args[1] = {(void *)&pl->small};
     hipKernelNodeParams kp =
         kernel_params(reinterpret_cast<void *>(pl->small_fn), pl->small.ntiles, args);
-    pl->small_stale = false;
     if (!pl->sexec) {
         if (hipGraphCreate(&pl->sgraph, 0) != hipSuccess ||
             hipGraphAddKernelNode(&pl->snode, pl->sgraph, nullptr, 0, &kp) != hipSuccess ||
-            hipGraphInstantiate(&pl->sexec, pl->sgraph, nullptr, nullptr, 0) != hipSuccess)
+            hipGraphInstantiate(&pl->sexec, pl->sgraph, nullptr, nullptr, 0) != hipSuccess) {
+            drop_graph(pl->sgraph, pl->sexec);
             return BN_ERR_DEVICE;
-        return BN_OK;
+        }
+    } else if (hipGraphExecKernelNodeSetParams(pl->sexec, pl->snode, &kp) != hipSuccess) {
+        return BN_ERR_DEVICE;
     }
-    return hipGraphExecKernelNodeSetParams(pl->sexec, pl->snode, &kp) == hipSuccess
-               ? BN_OK
-               : BN_ERR_DEVICE;
+    pl->small_stale = false;
+    return BN_OK;
 }
 
 // Write `frames` into the staging copy `k` and send it to the device on

@@ -31,3 +31,29 @@ for f in fr:
 assert L.bn_batch_plan_update(h, fr, 20, None) == 0
 assert "alloc" not in log()
 """)
+
+
+def test_a_failed_instantiation_is_tried_again(so):
+    """A graph that could not be instantiated leaves nothing behind, and the
+    next run makes it."""
+    fake_hip.run(so, r"""
+for odd in ((479, 637), (480, 640)):
+    for small in (False, True):      # a table's graph, a small list's
+        n = 3 if small else 20
+        h = create([(480, 640)] * 20)
+        shapes = [(480, 640)] * (n - 1) + [odd]
+        if small:
+            assert update(h, shapes) == 0
+            fake.fake_fail_instantiate(1)
+            assert L.bn_batch_run(h, None) != 0
+        else:
+            fake.fake_fail_instantiate(1)
+            if update(h, shapes) == 0:
+                L.bn_batch_run(h, None)
+            fake.fake_fail_instantiate(0)
+        log()
+        assert L.bn_batch_run(h, None) == 0
+        assert len(launches(log())) == (1 if small else 2)
+        L.bn_batch_plan_destroy(h)
+        assert fake.fake_graphs() == 0
+""")
