@@ -320,9 +320,11 @@ int bn_normals_vjp_stack(const float *depth, int32_t n, int32_t height, int32_t 
  *   an asynchronous copy on `stream`, ordered after earlier work and before
  *   later runs on that stream.  The instantiated graph is kept; its kernel
  *   nodes' launch parameters (grid, table sizes) are updated in place by the
- *   next bn_batch_run.  A list with more tiles than the plan's tables hold
- *   grows them, which first synchronises `stream` (the plan's earlier runs
- *   must have finished).
+ *   next bn_batch_run.  A plan holds one graph for lists whose frames all
+ *   take vector or scalar tiles and one for lists with tiles for any layout;
+ *   the second is instantiated by the first update that needs it.  A list
+ *   with more tiles than the plan's tables hold grows them, which first
+ *   synchronises `stream` (the plan's earlier runs must have finished).
  * bn_batch_run: one replay of the plan's graph over the current frame list
  *   on `stream`.
  * bn_batch_launch: the same kernels (two, or one for a small list), with

@@ -270,8 +270,8 @@ struct bn_batch_plan {
     hipEvent_t staged[2] = {nullptr, nullptr};
     int next = 0;                  // staging copy the next update writes
     uint32_t *dcounts = nullptr;   // 4 wavefront counts per tile (tile_capacity tiles)
-    // one graph per tile kernel, made when a list first needs it: [0] for lists
-    // without flat tiles, [1] with
+    // one graph per tile kernel, made by the create or update that first brings
+    // such a list: [0] for lists without flat tiles, [1] with
     struct TableGraph {
         hipGraph_t graph = nullptr;
         hipGraphExec_t exec = nullptr;
@@ -737,9 +737,10 @@ int bn_batch_plan_update(bn_batch_plan *plan, const bn_frame *frames_host, int32
     plan->next = 1 - k;
     plan->total_units = units;
     plan->total_pixels = pixels;
-    // new header values, grids and pointers reach the graph at its next run
+    // new header values, grids and pointers reach the graph at its next run; a
+    // graph that this kind of list does not have yet is made here, not there
     for (auto &g : plan->graphs) g.stale = true;
-    return BN_OK;
+    return plan->graphs[plan->has_flat].exec ? BN_OK : refresh_node(plan);
 }
 
 int bn_batch_run(bn_batch_plan *plan, void *stream) {

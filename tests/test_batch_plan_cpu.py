@@ -57,3 +57,23 @@ for odd in ((479, 637), (480, 640)):
         L.bn_batch_plan_destroy(h)
         assert fake.fake_graphs() == 0
 """)
+
+
+def test_a_run_instantiates_nothing(so):
+    """The graph of another kind of list is made by the update that brings the
+    list, once."""
+    fake_hip.run(so, r"""
+h = create([(480, 640)] * 20)
+log()
+made = 0
+for odd in ((480, 640), (479, 637), (480, 640), (479, 637)):
+    assert update(h, [(480, 640)] * 19 + [odd]) == 0
+    made += log().count("instantiate")
+    for _ in range(2):
+        assert L.bn_batch_run(h, None) == 0
+        lines = log()
+        assert "instantiate" not in lines, odd
+        name, grid = launches(lines)[0]
+        assert ("Lb1E" in name) == (odd == (479, 637)), (name, odd)
+assert made == 1
+""")
