@@ -333,7 +333,10 @@ int bn_normals_vjp_stack(const float *depth, int32_t n, int32_t height, int32_t 
  *   microseconds), so it suits small, latency-bound batches such as a
  *   server's; a long batch is the same either way.  Runs of one plan must
  *   not overlap (they share its descriptors and count work areas).
- * bn_batch_plan_info: pixels, tiles and workgroups of the current list.
+ * bn_batch_plan_info: the current list's pixels; its size in tiles of 256
+ *   work items (of four pixels in vector layouts, of one pixel in any other;
+ *   tiles for any layout take four there too, but the list's size and its
+ *   limits stay in this unit); and the workgroups of its launch.
  * bn_batch_plan_destroy: frees the plan; the caller makes sure no run of it
  *   is still in flight.
  */

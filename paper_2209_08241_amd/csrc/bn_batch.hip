@@ -788,9 +788,7 @@ int bn_batch_plan_info(const bn_batch_plan *plan, int64_t *n_pixels, int64_t *n_
     if (n_pixels) *n_pixels = (int64_t)plan->total_pixels;
     if (n_tiles) *n_tiles = (int64_t)plan->total_units;
     if (n_workgroups)
-        *n_workgroups = (int32_t)(plan->small_mode
-                                      ? plan->total_units
-                                      : grid_for(plan->total_units, plan->cus, plan->shape));
+        *n_workgroups = (int32_t)(plan->small_mode ? plan->small.ntiles : plan->grid);
     return BN_OK;
 }
 

@@ -77,3 +77,24 @@ for odd in ((480, 640), (479, 637), (480, 640), (479, 637)):
         assert ("Lb1E" in name) == (odd == (479, 637)), (name, odd)
 assert made == 1
 """)
+
+
+def test_plan_info_reports_the_launch(so):
+    """Workgroups are those of the launch, whatever tiles the frames take."""
+    fake_hip.run(so, r"""
+def info(h):
+    px, tiles, wg = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int32()
+    assert L.bn_batch_plan_info(h, ctypes.byref(px), ctypes.byref(tiles), ctypes.byref(wg)) == 0
+    return px.value, tiles.value, wg.value
+
+for shapes in ([(479, 637)] * 20, [(480, 640)] * 20, [(479, 637), (720, 1280)] * 12,
+               [(1079, 1917)] * 3, [(480, 640)] * 16, [(0, 5), (479, 637)]):
+    h = create(shapes)
+    log()
+    assert L.bn_batch_launch(h, None) == 0
+    px, tiles, wg = info(h)
+    assert px == sum(H * W for H, W in shapes)
+    assert wg == launches(log())[0][1], shapes
+    # the list's size: work items of four pixels in vector layouts, else of one
+    assert tiles == sum((H * (W // 4 if W % 4 == 0 else W) + 255) // 256 for H, W in shapes)
+""")
