@@ -386,8 +386,10 @@ int bn_estimate_normals_batch_noalloc(const bn_frame *frames_host, int32_t n_fra
  *   per workgroup or a software-pipelined pair - on a ring of scratch frames
  *   of height x width (allocated and freed here, about 512 MiB, a synthetic
  *   scene with steps, noise and holes) and records the fastest; later calls
- *   with params->variant == 0 on frames of that size class use it.
- *   Synchronous.
+ *   with params->variant == 0 on frames of that size class use it, except
+ *   those above 2^20 pixels that no vector tiles serve: they take the tiles
+ *   for any layout, which are timed for such a height x width and reported as
+ *   the scalar variant.  Synchronous.
  * bn_batch_plan_autotune: times the plan's launch over its grid shapes - a
  *   flat grid of one tile per workgroup (*best_shape = 0), of two or four
  *   consecutive tiles per workgroup (-2, -4), or 2, 4 or 8 persistent

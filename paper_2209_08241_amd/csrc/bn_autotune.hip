@@ -230,14 +230,17 @@ int bn_autotune_plain(int32_t height, int32_t width, const bn_params *params, in
     // more than kMargin (choices within run-to-run noise would otherwise flip
     // between runs).
     constexpr float kMargin = 0.97f;
-    const int dflt =
-        default_plain_variant(params, px, vec4_layout(d[0], width, width, n[0], m[0]));
+    const bool vec = vec4_layout(d[0], width, width, n[0], m[0]);
+    const int dflt = default_plain_variant(params, px, vec);
+    // where calls with variant 0 take flat tiles, which are no variant of their
+    // own, those are timed (and recorded as the scalar tiles they replace)
+    const bool flat = plain_takes_flat(params, px, vec, width, n[0], m[0]);
     int best = 0;
     float best_t = 1e30f, dflt_t = 1e30f;
     const int reps = ring * ((px < (1u << 20)) ? 8 : 3);
     for (int v = 1; v <= (int)VAR_COUNT; ++v) {
         bn_params p = *params;
-        p.variant = (uint32_t)v;
+        p.variant = flat && v == VAR_SCALAR ? (uint32_t)VAR_AUTO : (uint32_t)v;
         if (!bn_variant_supported(v, d[0], height, width, width, n[0], m[0])) continue;
         bool ok = true;
         for (int k = 0; k < ring && ok; ++k)  // warm-up

@@ -74,6 +74,12 @@ int default_plain_variant(const bn_params *p, uint64_t pixels, bool vec_layout) 
     return pixels <= small ? VAR_SCALAR : VAR_VEC4;
 }
 
+bool plain_takes_flat(const bn_params *p, uint64_t pixels, bool vec_layout, int32_t W,
+                      const float *normals, const uint8_t *mask) {
+    return !(vec_layout && method_has_vec4(p)) && pixels > kSmallRagged &&
+           flat_layout(W, normals, mask);
+}
+
 int check_frame_args(const float *depth, int32_t H, int32_t W, int64_t stride, float fx,
                      float fy, float cx, float cy, const float *normals, const uint8_t *mask) {
     if (H < 0 || W < 0) return BN_ERR_INVALID_ARG;
@@ -153,8 +159,8 @@ static int pick_variant(const float *depth, int32_t H, int32_t W, int64_t stride
                         const float *normals, const uint8_t *mask, const bn_params *p) {
     const uint64_t px = (uint64_t)H * (uint64_t)W;
     const bool vec = vec4_layout(depth, W, stride, normals, mask);
-    if (!(vec && method_has_vec4(p)))
-        return px > kSmallRagged && flat_layout(W, normals, mask) ? VAR_FLAT : VAR_SCALAR;
+    if (plain_takes_flat(p, px, vec, W, normals, mask)) return VAR_FLAT;
+    if (!(vec && method_has_vec4(p))) return VAR_SCALAR;
     const int tuned = tuned_plain_variant(p->method, p->alpha, px);
     if (tuned > 0 && method_variant_ok(p, tuned, depth, W, stride, normals, mask)) return tuned;
     return default_plain_variant(p, px, vec);

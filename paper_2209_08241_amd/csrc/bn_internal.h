@@ -68,6 +68,8 @@ int default_plain_variant(const bn_params *p, uint64_t pixels, bool vec_layout);
 // against flat, four-pair: 637x479 3.9 / 4.7 us, 1277x719 5.7 / 5.7, 1103x1021
 // 6.6 / 5.9, 1917x1079 9.7 / 8.2, 2555x1429 15.5 / 12.8.
 constexpr uint64_t kSmallRagged = 1u << 20;
+bool plain_takes_flat(const bn_params *p, uint64_t pixels, bool vec_layout, int32_t W,
+                      const float *normals, const uint8_t *mask);
 // Per-frame kernel arguments (derived constants included); work = NULL (the
 // caller sets the count work area when stats is given).
 void fill_frame_args(FrameArgs &f, const float *depth, int32_t H, int32_t W, int64_t stride,

@@ -98,3 +98,27 @@ for shapes in ([(479, 637)] * 20, [(480, 640)] * 20, [(479, 637), (720, 1280)] *
     # the list's size: work items of four pixels in vector layouts, else of one
     assert tiles == sum((H * (W // 4 if W % 4 == 0 else W) + 255) // 256 for H, W in shapes)
 """)
+
+
+@pytest.mark.parametrize("H,W,kernel", [(1429, 2555, "k_flat"), (719, 1277, "k_scalar"),
+                                        (1080, 1920, "k_vec4")])
+def test_plain_autotuning_times_what_a_call_takes(so, H, W, kernel):
+    """The kernels that the autotuner times are those that later calls with
+    variant 0 choose among."""
+    fake_hip.run(so, f"""
+H, W, kernel = {H}, {W}, "{kernel}"
+""" + r"""
+L.bn_autotune_reset()
+p = bn.make_params(2)
+d, n, m = (1 << 30), (2 << 30), (3 << 30)
+call = lambda: L.bn_estimate_normals(d, H, W, W, 500.0, 500.0, W / 2, H / 2, p, n, m, None, None)
+assert call() == 0
+(used, grid), = launches(log())
+assert kernel in used
+v, us = ctypes.c_int(), ctypes.c_float()
+assert L.bn_autotune_plain(H, W, p, ctypes.byref(v), ctypes.byref(us)) == 0
+timed = {name for name, _ in launches(log()) if "tune_scene" not in name and "zero" not in name}
+assert used in timed and (W % 4 == 0 or len(timed) == 1), (used, timed)
+assert call() == 0
+assert launches(log())[0][0] in timed
+""")
