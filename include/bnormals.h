@@ -270,7 +270,8 @@ int bn_normals_vjp(const float *depth, int32_t height, int32_t width, int64_t de
  * 1 <= n <= BN_MAX_STACK (n = 0, height 0 or width 0: nothing to do).
  * params->variant: 0 (vector tiles when the layout allows them, which
  * needs depth_frame_stride % 4 == 0 besides the single-frame rules, else
- * tiles of four pixels per thread for any layout), 1
+ * tiles of four pixels per thread for any layout, or scalar tiles where the
+ * stack has few pixels), 1
  * ("scalar") or 2 ("vec4") for the forward; 0 for the adjoint.
  * Errors as for the single-frame calls; BN_ERR_UNSUPPORTED for n >
  * BN_MAX_STACK.  Nothing is allocated; the arguments travel in the launch.

@@ -80,6 +80,23 @@ bool plain_takes_flat(const bn_params *p, uint64_t pixels, bool vec_layout, int3
            flat_layout(W, normals, mask);
 }
 
+// Scalar against flat tiles, buffers beyond the last-level cache, at 200, 300,
+// 400, 500, 620 and 800 thousand pixels (time of scalar over time of flat).
+// Four-pair: 1 frame 0.89 0.96 1.00 1.08 1.11 1.17, 2 frames 0.91 1.00 1.16
+// 1.21 1.29 1.35, 16 frames 1.06 1.15 1.22 1.28 1.28 1.35.  Pair removal: 1
+// 0.79 0.87 0.91 0.95 1.01 1.04, 2 0.83 0.92 0.97 1.05 1.13 1.17, 16 0.91
+// 1.01 1.08 1.15 1.14 1.24.  Multi-scale, K = 3: 1 0.71 0.74 0.80 0.90 0.95
+// 0.99, 2 0.78 0.80 0.89 1.03 1.07 1.11, 16 0.81 0.92 0.99 1.09 1.00 1.11 (K =
+// 1 and 6 between 0.07 above and 0.10 below).  A single frame's line lies half
+// as high again.  (One frame of 637x479 in multi-scale: 5.1 us scalar, 6.9
+// flat.)
+bool stack_takes_flat(const bn_params *p, uint32_t n, uint64_t pixels) {
+    const uint64_t line = p->method == BN_METHOD_FOUR_PAIR      ? 1u << 18
+                          : p->method == BN_METHOD_PAIR_REMOVAL ? 3u << 17
+                                                                : 1u << 19;
+    return pixels > (n == 1 ? line + line / 2 : line);
+}
+
 int check_frame_args(const float *depth, int32_t H, int32_t W, int64_t stride, float fx,
                      float fy, float cx, float cy, const float *normals, const uint8_t *mask) {
     if (H < 0 || W < 0) return BN_ERR_INVALID_ARG;

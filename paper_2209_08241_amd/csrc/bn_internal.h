@@ -70,6 +70,10 @@ int default_plain_variant(const bn_params *p, uint64_t pixels, bool vec_layout);
 constexpr uint64_t kSmallRagged = 1u << 20;
 bool plain_takes_flat(const bn_params *p, uint64_t pixels, bool vec_layout, int32_t W,
                       const float *normals, const uint8_t *mask);
+// A stack of n frames, `pixels` together, that the vector tiles don't serve
+// takes the flat tiles above a number of pixels (the latency chain as for
+// single frames, one longer per tile in pair removal and with each scale).
+bool stack_takes_flat(const bn_params *p, uint32_t n, uint64_t pixels);
 // Per-frame kernel arguments (derived constants included); work = NULL (the
 // caller sets the count work area when stats is given).
 void fill_frame_args(FrameArgs &f, const float *depth, int32_t H, int32_t W, int64_t stride,

@@ -137,7 +137,8 @@ extern "C" int bn_estimate_normals_stack(const float *depth, int32_t n, int32_t 
     s.kind = kTileScalar;
     if (v == VAR_VEC4 || (v == VAR_AUTO && vec_ok)) {
         s.kind = kTileVec4;
-    } else if (v == VAR_AUTO && flat_layout(width, normals, mask)) {
+    } else if (v == VAR_AUTO && flat_layout(width, normals, mask) &&
+               stack_takes_flat(params, s.n, (uint64_t)s.n * s.f.npix)) {
         s.kind = kTileFlat;
     }
     if (s.kind != kTileScalar) {

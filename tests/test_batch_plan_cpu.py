@@ -122,3 +122,27 @@ assert used in timed and (W % 4 == 0 or len(timed) == 1), (used, timed)
 assert call() == 0
 assert launches(log())[0][0] in timed
 """)
+
+
+@pytest.mark.parametrize("method,scales,line", [("four_pair", 0, 1 << 18),
+                                                ("pair_removal", 0, 3 << 17),
+                                                ("multiscale", 3, 1 << 19)])
+def test_small_stacks_of_odd_frames_take_scalar_tiles(so, method, scales, line):
+    """Up to `line` pixels in all (half as many again for a single frame)."""
+    fake_hip.run(so, f"""
+method, scales, line = "{method}", {scales}, {line}
+""" + r"""
+p = bn.make_params(2, method=method, scales=scales)
+intr = (bn.Intrinsics * 64)(*[bn.Intrinsics(500.0, 500.0, 50.0, 50.0)] * 64)
+d, n, m = (1 << 30), (2 << 30), (3 << 30)
+for frames_, most in ((1, line * 3 // 2), (2, line), (64, line)):
+    for W in (129, 255):
+        H = most // (frames_ * W)       # the largest height up to the line
+        for h, flat in ((H, False), (H + 1, True)):
+            assert L.bn_estimate_normals_stack(d, frames_, h, W, W, h * W, intr, p, n, m, None,
+                                               None) == 0
+            (name, grid), = launches(log())
+            assert ("k_stack_flat" in name) == flat, (frames_, h, W, name)
+            if not flat:
+                assert "k_stack" in name and grid == frames_ * ((h * W + 255) // 256)
+""")
