@@ -311,12 +311,27 @@ size_t buffer_bytes(int32_t capacity, uint64_t tile_capacity) {
     return table_offset(capacity) + sizeof(uint32_t) * (size_t)tile_capacity;
 }
 
-// The tiles of this frame under these parameters.  (A list fills the chip
-// together, so the flat tiles serve its small frames too.)
-uint32_t frame_kind(const bn_frame &s, const bn_params *p) {
+// The tiles of this frame under these parameters; flat: the list's rule
+// (list_takes_flat).
+uint32_t frame_kind(const bn_frame &s, const bn_params *p, bool flat) {
     if (method_has_vec4(p) && vec4_layout(s.depth, s.width, s.depth_stride, s.normals, s.mask))
         return kTileVec4;
-    return flat_layout(s.width, s.normals, s.mask) ? kTileFlat : kTileScalar;
+    return flat && flat_layout(s.width, s.normals, s.mask) ? kTileFlat : kTileScalar;
+}
+
+// Lists that hold frames no vector tiles serve take flat tiles for them above a
+// number of pixels in all (scalar against flat tiles, buffers beyond the
+// last-level cache; lists of 1, 4 and 16 frames, in us.  Four-pair: 300
+// thousand pixels 4.6 4.8 4.9 / 5.1 5.1 5.2, 500 5.4 5.5 5.6 / 5.4 5.6 5.3, 620
+// 6.1 6.2 6.3 / 5.6 5.7 5.7.  Pair removal: 620 6.7 6.7 6.8 / 6.9 7.1 7.1, 800
+// 7.4 7.5 7.6 / 7.4 7.6 7.7, 1000 8.3 8.4 9.2 / 7.8 7.9 8.3.  Multi-scale, K =
+// 3: 300 5.4 5.6 5.6 / 7.5 7.6 7.3, 800 8.2 8.3 8.5 / 8.7 9.3 9.5, 1000 9.3
+// 9.4 10.0 / 9.2 9.5 10.0).  The lists' kernels carry every tile body, so the
+// lines lie higher than a stack's.
+bool list_takes_flat(const bn_params *p, uint64_t pixels) {
+    return pixels > (p->method == BN_METHOD_FOUR_PAIR      ? 1u << 19
+                     : p->method == BN_METHOD_PAIR_REMOVAL ? 3u << 18
+                                                           : 1u << 20);
 }
 
 // fill_frame_args' pixels per work item.
@@ -337,14 +352,18 @@ int count_frames(const bn_frame *frames, int32_t n, const bn_params *p, uint64_t
                                   s.cy, s.normals, s.mask);
         if (rc == BN_OK) rc = check_stats_arg(s.stats);
         if (rc != BN_OK) return rc;
+        px += (uint64_t)s.height * (uint64_t)s.width;
+    }
+    const bool flat = list_takes_flat(p, px);
+    for (int32_t k = 0; k < n; ++k) {
+        const bn_frame &s = frames[k];
         if (s.height > 0 && s.width > 0) {
-            const uint32_t kind = frame_kind(s, p);
+            const uint32_t kind = frame_kind(s, p, flat);
             FrameArgs f;
             fill_frame_args(f, s.depth, s.height, s.width, s.depth_stride, s.fx, s.fy, s.cx, s.cy,
                             p, s.normals, s.mask, s.stats, kind_items(kind));
             t += ((uint64_t)f.nitems + kBlock - 1) / kBlock;
             u += ((uint64_t)(kind == kTileVec4 ? f.nitems : f.npix) + kBlock - 1) / kBlock;
-            px += (uint64_t)s.height * (uint64_t)s.width;
         }
     }
     if (u > 0x7fffffffull) return BN_ERR_UNSUPPORTED;
@@ -372,18 +391,19 @@ bool chunk_ok(uint64_t units, int cus, int32_t shape) {
 }
 
 // Host image of the descriptors of `frames` (already validated) in `base`.
-int build_table(const bn_frame *frames, int32_t n, const bn_params *p, int32_t capacity,
-                uint32_t grid, WorkArea *work, uint32_t *count_chunks, int *has_flat,
-                void *base) {
+int build_table(const bn_frame *frames, int32_t n, const bn_params *p, uint64_t pixels,
+                int32_t capacity, uint32_t grid, WorkArea *work, uint32_t *count_chunks,
+                int *has_flat, void *base) {
     auto *hdr = static_cast<BatchHeader *>(base);
     auto *fr = reinterpret_cast<BatchFrame *>(hdr + 1);
     auto *tf = reinterpret_cast<uint32_t *>(static_cast<char *>(base) + table_offset(capacity));
+    const bool flat = list_takes_flat(p, pixels);
     uint64_t tiles = 0;
     *count_chunks = 1;
     *has_flat = 0;
     for (int32_t k = 0; k < n; ++k) {
         const bn_frame &s = frames[k];
-        const uint32_t kind = frame_kind(s, p);
+        const uint32_t kind = frame_kind(s, p, flat);
         BatchFrame b;
         std::memset(&b, 0, sizeof(b));
         uint64_t nt = 0;
@@ -414,13 +434,14 @@ int build_table(const bn_frame *frames, int32_t n, const bn_params *p, int32_t c
 // The kernel-argument image of a small list (already validated); frame k
 // reduces its counts on work[k].
 void fill_small(SmallBatch &sb, const bn_frame *frames, int32_t n, const bn_params *params,
-                WorkArea *work) {
+                uint64_t pixels, WorkArea *work) {
     std::memset(&sb, 0, sizeof(sb));
+    const bool flat = list_takes_flat(params, pixels);
     uint32_t tiles = 0;
     for (int k = 0; k < kSmallFrames; ++k) sb.tile_begin[k] = UINT32_MAX;
     for (int32_t k = 0; k < n; ++k) {
         const bn_frame &s = frames[k];
-        const uint32_t kind = frame_kind(s, params);
+        const uint32_t kind = frame_kind(s, params, flat);
         uint32_t nt = 0;
         if (s.height > 0 && s.width > 0) {
             fill_frame_args(sb.f[k], s.depth, s.height, s.width, s.depth_stride, s.fx, s.fy, s.cx,
@@ -437,8 +458,8 @@ void fill_small(SmallBatch &sb, const bn_frame *frames, int32_t n, const bn_para
     sb.ntiles = tiles;
 }
 
-void build_small(bn_batch_plan *pl, const bn_frame *frames, int32_t n) {
-    fill_small(pl->small, frames, n, &pl->params, pl->work);
+void build_small(bn_batch_plan *pl, const bn_frame *frames, int32_t n, uint64_t pixels) {
+    fill_small(pl->small, frames, n, &pl->params, pixels, pl->work);
 }
 
 hipKernelNodeParams kernel_params(void *func, dim3 grid, void **args) {
@@ -574,8 +595,8 @@ int refresh_small_node(bn_batch_plan *pl) {
 // Write `frames` into the staging copy `k` and send it to the device on
 // `stream` (header, descriptors and the used part of the tile table).
 int upload(bn_batch_plan *pl, const bn_frame *frames, int32_t n, int k, hipStream_t stream,
-           uint64_t tiles) {
-    int rc = build_table(frames, n, &pl->params, pl->capacity, pl->grid, pl->work,
+           uint64_t tiles, uint64_t pixels) {
+    int rc = build_table(frames, n, &pl->params, pixels, pl->capacity, pl->grid, pl->work,
                          &pl->count_chunks, &pl->has_flat, pl->staging[k]);
     if (rc != BN_OK) return rc;
     pl->hdr = *static_cast<const BatchHeader *>(pl->staging[k]);
@@ -659,8 +680,8 @@ int bn_batch_plan_create(const bn_frame *frames_host, int32_t n_frames, const bn
     // tables for the list in any layout (`units`, never fewer than its tiles),
     // so that later lists of no more pixels fit whatever their frames' layout
     rc = alloc_buffers(pl, units > 0 ? units : 1);
-    if (rc == BN_OK) rc = build_table(frames_host, n_frames, params, pl->capacity, pl->grid,
-                                      pl->work, &pl->count_chunks, &pl->has_flat,
+    if (rc == BN_OK) rc = build_table(frames_host, n_frames, params, pixels, pl->capacity,
+                                      pl->grid, pl->work, &pl->count_chunks, &pl->has_flat,
                                       pl->staging[0]);
     if (rc == BN_OK) pl->hdr = *static_cast<const BatchHeader *>(pl->staging[0]);
     if (rc == BN_OK &&
@@ -673,7 +694,7 @@ int bn_batch_plan_create(const bn_frame *frames_host, int32_t n_frames, const bn
     }
     pl->next = 1;  // staging[0] holds the current table
     if (n_frames <= kSmallFrames) {
-        build_small(pl, frames_host, n_frames);
+        build_small(pl, frames_host, n_frames, pixels);
         pl->small_mode = true;
         pl->small_stale = true;
     }
@@ -691,7 +712,7 @@ int bn_batch_plan_update(bn_batch_plan *plan, const bn_frame *frames_host, int32
     if (rc != BN_OK) return rc;
     if (n_frames <= kSmallFrames) {
         // descriptors in the kernel arguments: nothing to upload
-        build_small(plan, frames_host, n_frames);
+        build_small(plan, frames_host, n_frames, pixels);
         plan->small_mode = true;
         plan->small_stale = true;
         plan->total_units = units;
@@ -732,7 +753,7 @@ int bn_batch_plan_update(bn_batch_plan *plan, const bn_frame *frames_host, int32
     // the staging copy may still feed the upload issued two updates ago
     if (hipEventSynchronize(plan->staged[k]) != hipSuccess) return BN_ERR_DEVICE;
     plan->grid = grid;
-    rc = upload(plan, frames_host, n_frames, k, s, tiles);
+    rc = upload(plan, frames_host, n_frames, k, s, tiles, pixels);
     if (rc != BN_OK) return rc;
     plan->next = 1 - k;
     plan->total_units = units;
@@ -935,7 +956,7 @@ extern "C" int bn_estimate_normals_batch_noalloc(const bn_frame *frames_host, in
     rc = scratch_for_current_device(&work);
     if (rc != BN_OK) return rc;
     SmallBatch sb;
-    fill_small(sb, frames_host, n_frames, params, work);
+    fill_small(sb, frames_host, n_frames, params, pixels, work);
     hipStream_t s = (hipStream_t)stream;
     // the work areas must start at zero: a fill kernel (graph-capture safe)
     const uint32_t words = (uint32_t)((size_t)n_frames * sizeof(WorkArea) / 8);

@@ -146,3 +146,35 @@ for frames_, most in ((1, line * 3 // 2), (2, line), (64, line)):
             if not flat:
                 assert "k_stack" in name and grid == frames_ * ((h * W + 255) // 256)
 """)
+
+
+@pytest.mark.parametrize("method,scales,line", [("four_pair", 0, 1 << 19),
+                                                ("pair_removal", 0, 3 << 18),
+                                                ("multiscale", 3, 1 << 20)])
+def test_small_lists_of_odd_frames_take_scalar_tiles(so, method, scales, line):
+    """Up to `line` pixels in the whole list: by a plan, for a small list and a
+    table, and without one."""
+    fake_hip.run(so, f"""
+method, scales, line = "{method}", {scales}, {line}
+""" + r"""
+p = bn.make_params(2, method=method, scales=scales)
+for n in (1, 3, 15, 16, 40):
+    for W in (131, 255):
+        H = line // (n * W)
+        # a frame more of whole groups takes the list to the line, or over it
+        rest = (line - n * H * W) // 4
+        for extra, flat in ((rest, False), (rest + 1, True)):
+            shapes = [(H, W)] * n + [(1, 4 * extra)]
+            scalar = sum((h * w // (4 if w % 4 == 0 else 1) + 255) // 256 for h, w in shapes)
+            h = create(shapes, p)
+            log()
+            assert L.bn_batch_launch(h, None) == 0
+            (name, grid) = launches(log())[0]
+            assert (grid < scalar) == flat, (shapes[0], n, extra, grid, scalar)
+            if len(shapes) > 16:
+                assert ("Lb1E" in name) == flat
+            else:
+                assert L.bn_estimate_normals_batch_noalloc(frames(shapes), len(shapes), p, None) == 0
+                assert launches(log())[1] == (name, grid)
+            L.bn_batch_plan_destroy(h)
+""")

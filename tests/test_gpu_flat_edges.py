@@ -43,3 +43,35 @@ def test_stacks_equal_scalar_tiles(method, alpha, K, H, W, shift):
         out.append((n, m, st))
     for x, y in zip(*out):
         assert torch.equal(x.reshape(-1).view(torch.uint8), y.reshape(-1).view(torch.uint8))
+
+
+@pytest.mark.parametrize("method,alpha,K", METHODS)
+@pytest.mark.parametrize("n", [9, 30])
+def test_lists_of_small_frames_beside_a_large_one(method, alpha, K, n):
+    """A list of more than 2^20 pixels: its small frames of any layout take flat
+    tiles (and scalar ones where the codes start elsewhere in a word than the
+    normals), as single frames give them."""
+    import torch
+    big = torch.from_numpy(depths(1032, 1024, 3)).cuda()
+    frames = [bn.BatchFrame(big, 90.0, 92.0, 500.0, 500.0)]
+    shapes = [(1, 4), (7, 5), (33, 75), (3, 257), (61, 131), (2, 1030), (19, 9), (40, 255)]
+    for k in range(n):
+        H, W = shapes[k % 8]
+        d = torch.from_numpy(depths(H, W, k)).cuda()
+        out = torch.full((3 * H * W + 32,), 7.0, device="cuda")
+        m = torch.full((H * W + 32,), 99, dtype=torch.uint8, device="cuda")
+        at = k % 7
+        frames.append(bn.BatchFrame(d, 90.0, 92.0, W / 2, H / 2,
+                                    normals=out[3 * at:3 * at + 3 * H * W].view(H, W, 3),
+                                    mask=m[at + k // 8:at + k // 8 + H * W].view(H, W)))
+        frames[-1].buffers = (out, 3 * at, 7.0), (m, at + k // 8, 99)
+    with bn.BatchPlan(frames, alpha, method=method, scales=K) as plan:
+        plan.run()
+        torch.cuda.synchronize()
+    for f in frames[1:]:
+        want = bn.estimate_normals(f.depth, 90.0, 92.0, f.cx, f.cy, alpha, method=method, scales=K,
+                                   variant=1)
+        for x, y in zip((f.normals, f.mask, f.stats), want):
+            assert torch.equal(x.reshape(-1).view(torch.uint8), y.reshape(-1).view(torch.uint8))
+        for (buf, at, v), x in zip(f.buffers, (f.normals, f.mask)):
+            assert bool((buf[:at] == v).all()) and bool((buf[at + x.numel():] == v).all())
