@@ -66,7 +66,10 @@ int default_plain_variant(const bn_params *p, uint64_t pixels, bool vec_layout);
 // pixels take the flat tiles, smaller ones the scalar tiles (one frame of few
 // tiles is a chain of latencies, shorter with more wavefronts).  Scalar
 // against flat, four-pair: 637x479 3.9 / 4.7 us, 1277x719 5.7 / 5.7, 1103x1021
-// 6.6 / 5.9, 1917x1079 9.7 / 8.2, 2555x1429 15.5 / 12.8.
+// 6.6 / 5.9, 1917x1079 9.7 / 8.2, 2555x1429 15.5 / 12.8 on three sets of
+// buffers; on a ring beyond the last-level cache 1103x1021 6.7 / 6.0, 1917x1079
+// 9.6 / 8.4 (pair removal 10.4 / 9.5, multi-scale 12.8 / 10.8), 2555x1429 15.1
+// / 12.1, 4001x3001 41.8 / 29.6.
 constexpr uint64_t kSmallRagged = 1u << 20;
 bool plain_takes_flat(const bn_params *p, uint64_t pixels, bool vec_layout, int32_t W,
                       const float *normals, const uint8_t *mask);

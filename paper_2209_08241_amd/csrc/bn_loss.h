@@ -4,8 +4,9 @@
 // on `stream`, nothing allocated; arrays dense, floats 4-byte aligned.
 //   bn_cosine_loss: over the pixels U with mask == BN_VALID and target_mask ==
 //     BN_VALID, *loss = sum of (1 - normals . target) / *count and *count =
-//     max(|U|, 1), in binary32 (the sum in FP64, in a fixed order).  used (nullable) receives 1 for a pixel of U and 0 for the
-//     others.  workspace: BN_COSINE_WORKSPACE(pixels) doubles.
+//     max(|U|, 1), in binary32 (the sum in FP64, in a fixed order).  used
+//     (nullable) receives 1 for a pixel of U and 0 for the others.  workspace:
+//     BN_COSINE_WORKSPACE(pixels) doubles, 16-byte aligned.
 //   bn_cosine_loss_vjp: grad_normals = -(*grad / *count) target at the
 //     pixels of U, 0 times target at the others.
 // normals, target, grad_normals [pixels][3]; masks, used [pixels]; pixels up

@@ -224,8 +224,9 @@ def traffic(fetch_dir: str, write_dir: str, kernel: str, pixels: int, workload: 
 
 def launches(reps: int = 20) -> None:
     """Each kernel of interest `reps` times: the three methods on one
-    1920x1080 frame, then the stacked forward and adjoint (vector kernel, and
-    scalar tiles on a padded copy) on 16 x 640x480."""
+    1920x1080 frame, then the stacked forward and adjoint (vector kernel, also on
+    rows of stride 641) on 16 x 640x480, the adjoint of one of them (scalar
+    tiles), and pair removal on 12 x 1280x720."""
     sys.path.insert(0, ROOT)
     import numpy as np
     import torch
@@ -240,13 +241,18 @@ def launches(reps: int = 20) -> None:
     intr = [x.intrinsics for x in scs]
     st = torch.from_numpy(np.stack([x.depth for x in scs])).cuda()
     g = torch.randn((16, 480, 640, 3), device="cuda")
-    # the same stack with a row stride of 641: the adjoint's scalar tiles
+    # the same stack with a row stride of 641
     pad = torch.zeros((16, 480, 641), device="cuda")
     pad[:, :, :640] = st
     for _ in range(reps):
         bn.estimate_normals_stack(st, intr, want_stats=False)
         bn.normals_vjp_stack(st, intr, g)
         bn.normals_vjp_stack(pad[:, :, :640], intr, g)
+        bn.normals_vjp_stack(st[:1], intr[:1], g[:1])
+    hd = scenes.sized_frame(720, 1280, seed=3)
+    st = torch.from_numpy(np.stack([hd.depth] * 12)).cuda()
+    for _ in range(reps):
+        bn.estimate_normals_stack(st, hd.intrinsics, method="pair_removal", want_stats=False)
     torch.cuda.synchronize()
     print("launches done", flush=True)
 
@@ -415,9 +421,12 @@ _VALU_WHAT = {
     "bn::k_vec4<2, 1, 1>": ("pair removal, 1920x1080, alpha 2", 2073600),
     "bn::k_vec4<1, 1, 2>": ("multi-scale K=3, 1920x1080, alpha 1", 2073600),
     "bn::k_stack<2, 0>": ("four-pair stack, 16 x 640x480", 16 * 307200),
-    "bn::k_vjp4_stack<2, 4, 8>": ("adjoint stack, 16 x 640x480, vector kernel", 16 * 307200),
-    "bn::k_vjp_stack<2, 64, 16>": ("adjoint stack, 16 x 640x480, scalar tiles (row stride 641)",
-                                   16 * 307200),
+    "bn::k_stack<2, 1>": ("pair-removal stack, 12 x 1280x720", 12 * 921600),
+    "bn::k_vjp4_stack<2, 4, 8, false>": ("adjoint stack, 16 x 640x480, vector kernel",
+                                         16 * 307200),
+    "bn::k_vjp4_stack<2, 4, 8, true>": ("adjoint stack, 16 x 640x480, vector kernel, row "
+                                        "stride 641", 16 * 307200),
+    "bn::k_vjp_stack<2, 32, 8>": ("adjoint of one 640x480 frame, scalar tiles", 307200),
 }
 
 

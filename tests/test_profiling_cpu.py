@@ -75,3 +75,13 @@ def test_traffic_records_and_lookup(tmp_path, monkeypatch):
     assert bench.load_traffic("plainX", px, variant="vec4w64") is None
     monkeypatch.setattr(bench, "kernel_hash", lambda sources=None: "other")
     assert bench.load_traffic("plainX", px, variant="vec4") is None
+
+
+def test_the_counters_table_names_kernels_that_exist():
+    """Each row of the VALU counters' table is a kernel of the library."""
+    import subprocess
+    import paper_2209_08241_amd as bn
+    names = subprocess.run(["nm", "-C", bn.LIB_PATH], stdout=subprocess.PIPE, text=True,
+                           check=True).stdout
+    for kernel in profiling._VALU_WHAT:
+        assert kernel + "(" in names, kernel
