@@ -9,28 +9,24 @@ from test_gpu_flat_tiles import METHODS, depths
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("method,alpha,K", METHODS)
-@pytest.mark.parametrize("H,W,shift", [(2053, 4, (1, 0, 0)), (1641, 5, (3, 1, 1)), (1367, 6, (0, 9, 1)),
-                                       (1181, 7, (2, 4, 0)), (911, 9, (1, 3, 3)), (65, 131, (0, 2, 6)),
-                                       (33, 257, (3, 2, 2)), (17, 511, (0, 1, 5)), (9, 1030, (1, 0, 4)),
-                                       (2, 4111, (0, 7, 3)), (1, 8203, (2, 0, 4)), (40, 255, (1, 5, 1))])
-def test_stacks_equal_scalar_tiles(method, alpha, K, H, W, shift):
-    """64 frames, more than 2^19 pixels together, with padded rows; the depth,
-    the normals (in pixels) and the codes start `shift`
-    elements into larger buffers (alike in groups of four pixels, as flat
-    tiles ask), whose surroundings stay as they were."""
+N = 64
+
+
+def stacks_agree(method, alpha, K, H, W, shift, pad):
+    """64 frames, more than 2^19 pixels together, with padded rows, in flat tiles
+    and in scalar ones; the depth, the normals (in pixels) and the codes start
+    `shift` elements into larger buffers (alike in groups of four pixels, as
+    flat tiles ask), whose surroundings stay as they were."""
     import torch
-    N = 64
     assert N * H * W > 1 << 19 and (shift[1] - shift[2]) % 4 == 0
     one = np.stack([depths(H, W, H + k) for k in range(2)])
-    pad = W % 4
     wide = torch.full((N * H * (W + pad) + 8,), 3.25, device="cuda")
     d = wide[shift[0]:shift[0] + N * H * (W + pad)].view(N, H, W + pad)[:, :, :W]
     for k in range(N):   # frames differ: rolled rows
         d[k] = torch.from_numpy(np.ascontiguousarray(np.roll(one[k % 2], k, axis=0))).cuda()
     out = []
     for variant in (0, 1):
-        nb = torch.full((3 * N * H * W + 64,), 7.0, device="cuda")
+        nb = torch.full((3 * N * H * W + 128,), 7.0, device="cuda")
         mb = torch.full((N * H * W + 64,), 99, dtype=torch.uint8, device="cuda")
         n0 = 3 * shift[1]
         n = nb[n0:n0 + 3 * N * H * W].view(N, H, W, 3)
@@ -43,6 +39,22 @@ def test_stacks_equal_scalar_tiles(method, alpha, K, H, W, shift):
         out.append((n, m, st))
     for x, y in zip(*out):
         assert torch.equal(x.reshape(-1).view(torch.uint8), y.reshape(-1).view(torch.uint8))
+
+
+@pytest.mark.parametrize("method,alpha,K", METHODS)
+@pytest.mark.parametrize("H,W,shift", [(2053, 4, (1, 0, 0)), (1641, 5, (3, 1, 1)), (1367, 6, (0, 9, 1)),
+                                       (1181, 7, (2, 4, 0)), (911, 9, (1, 3, 3)), (65, 131, (0, 2, 6)),
+                                       (33, 257, (3, 2, 2)), (17, 511, (0, 1, 5)), (9, 1030, (1, 0, 4)),
+                                       (2, 4111, (0, 7, 3)), (1, 8203, (2, 0, 4)), (40, 255, (1, 5, 1))])
+def test_stacks_equal_scalar_tiles(method, alpha, K, H, W, shift):
+    stacks_agree(method, alpha, K, H, W, shift, W % 4)
+
+
+@pytest.mark.parametrize("W", [254, 255, 256, 259])
+@pytest.mark.parametrize("n,m", [(0, 0), (0, 4), (1, 1), (1, 5), (2, 6), (4, 0), (7, 3), (9, 1),
+                                 (31, 3)])
+def test_output_alignments(W, n, m):
+    stacks_agree("four_pair", 2, 0, 33, W, (n % 4, n, m), 1)
 
 
 @pytest.mark.parametrize("method,alpha,K", METHODS)
