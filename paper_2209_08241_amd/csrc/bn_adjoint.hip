@@ -443,23 +443,33 @@ static Vjp4StackFn vjp4_stack_kernel(const Vjp4Shape &sh, int a, bool ragged) {
 
 static bool aligned16(const void *p) { return ((uintptr_t)p % 16) == 0; }
 
-// The vector kernels take alpha <= 4 and rows of at least a group; rows of
-// whole, 16-byte aligned groups with streaming stores, any others as RAGGED.
-// Launches of few pixels stay with the scalar tiles: a band is a chain of RB
-// rows (2 alpha of them before its first output), and there are too few of
-// them to hide it (scalar against vector: alpha 2, 320x240 3.9 / 6.2 us,
-// 640x480 5.3 / 6.4, two of them 8.4 / 7.4, 1280x720 10.0 / 8.8; alpha 4,
-// 640x480 6.7 / 10.8, two 10.6 / 11.7, 1280x720 12.9 / 11.9).  As scalar
-// tiles, ragged frames took: four of 1277x719, alpha 2, 29.0 us, now 18.1.
-static bool vjp4_serves(int32_t n, int32_t H, int32_t W, int alpha) {
-    return alpha <= 4 && W >= 4 &&
-           (int64_t)n * H * W > (alpha <= 2 ? (int64_t)3 << 17 : (int64_t)3 << 18);
-}
-
+// Rows that are not whole, 16-byte aligned groups.
 static bool vjp4_ragged(const float *depth, int32_t W, int64_t stride, int64_t fstride,
                         const float *gn, const float *gd) {
     return !(W % 4 == 0 && stride % 4 == 0 && fstride % 4 == 0 && aligned16(depth) &&
              aligned16(gn) && aligned16(gd));
+}
+
+// The vector kernels take alpha <= 4 and rows of at least a group; rows of
+// whole, 16-byte aligned groups with streaming stores, any others as RAGGED.
+// Launches of few pixels stay with the scalar tiles: a band is a chain of RB
+// rows (2 alpha of them before its first output), and there are too few of
+// them to hide it.  Scalar against vector, aligned rows: alpha 2, 320x240 3.9 /
+// 6.2 us, 640x480 5.3 / 6.4, two of them 8.4 / 7.4, 1280x720 10.0 / 8.8; alpha
+// 4, 640x480 6.7 / 10.8, two 10.6 / 11.7, 1280x720 12.9 / 11.9.  Ragged rows,
+// at 400, 500, 620, 800, 1000 and 1500 thousand pixels, one frame: alpha 1 5.4
+// 5.9 7.4 8.2 9.2 13.4 / 7.6 7.7 7.9 8.0 9.5 10.2, alpha 2 6.1 6.6 8.6 9.5 10.7
+// 17.4 / 7.9 8.0 8.2 8.3 9.9 10.6, alpha 4 7.5 8.2 11.0 12.2 13.6 20.1 / - - -
+// 12.6 13.0 13.5 (alpha 3 crosses at 800: 11.1 / 10.9); eight frames: alpha 1
+// 6.0 7.7 8.2 9.0 9.7 13.1 / 7.9 8.0 8.2 9.7 9.9 12.8, alpha 2 6.7 8.7 9.2 10.1
+// 11.1 17.7 / 8.0 8.1 8.3 9.3 10.0 12.9.  Four of 1277x719, alpha 2: 29.0 / 18.1.
+static bool vjp4_serves(int32_t n, int32_t H, int32_t W, int alpha, bool ragged) {
+    if (alpha > 4 || W < 4) return false;
+    int64_t line = alpha <= 2 ? 3 << 17 : 3 << 18;
+    if (ragged && alpha == 1) line = 1 << 20;
+    if (ragged && alpha == 2) line = n == 1 ? 9 << 16 : 7 << 16;
+    if (ragged && alpha == 4) line = 7 << 17;
+    return (int64_t)n * H * W > line;
 }
 
 typedef void (*VjpFn)(FrameArgs, const float *, float *, uint32_t);
@@ -515,11 +525,10 @@ extern "C" int bn_normals_vjp(const float *depth, int32_t height, int32_t width,
     if (rc != BN_OK) return rc;
     if (height == 0 || width == 0) return BN_OK;
     if ((uintptr_t)grad_depth % 4) return BN_ERR_INVALID_ARG;
-    if (vjp4_serves(1, height, width, params->alpha)) {
+    const bool ragged = vjp4_ragged(depth, width, depth_stride, 0, grad_normals, grad_depth);
+    if (vjp4_serves(1, height, width, params->alpha, ragged)) {
         const Vjp4Shape sh = vjp4_shape(height, width, 1, params->alpha);
-        Vjp4Fn fn = vjp4_kernel(sh, params->alpha,
-                                vjp4_ragged(depth, width, depth_stride, 0, grad_normals,
-                                            grad_depth));
+        Vjp4Fn fn = vjp4_kernel(sh, params->alpha, ragged);
         if (!fn) return BN_ERR_UNSUPPORTED;
         FrameArgs f;
         fill_frame_args(f, depth, height, width, depth_stride, fx, fy, cx, cy, params, nullptr,
@@ -561,12 +570,11 @@ extern "C" int bn_normals_vjp_stack(const float *depth, int32_t n, int32_t heigh
     s.f.mask = nullptr;
     s.gn = grad_normals;
     s.gd = grad_depth;
-    if (vjp4_serves(n, height, width, params->alpha)) {
+    const bool ragged =
+        vjp4_ragged(depth, width, depth_stride, depth_frame_stride, grad_normals, grad_depth);
+    if (vjp4_serves(n, height, width, params->alpha, ragged)) {
         const Vjp4Shape sh = vjp4_shape(height, width, s.n, params->alpha);
-        Vjp4StackFn fn = vjp4_stack_kernel(sh, params->alpha,
-                                           vjp4_ragged(depth, width, depth_stride,
-                                                       depth_frame_stride, grad_normals,
-                                                       grad_depth));
+        Vjp4StackFn fn = vjp4_stack_kernel(sh, params->alpha, ragged);
         if (!fn) return BN_ERR_UNSUPPORTED;
         s.tiles_x = sh.strips;
         s.tiles_per_frame = sh.strips * sh.bands;
