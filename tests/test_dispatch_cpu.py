@@ -39,3 +39,13 @@ for n in (0, 1, 2, 64):              # 0: the single-frame call
             (name, grid), = launches(log())
             assert ("k_vjp4" in name) == vec, (n, W, h, name)
 """)
+
+
+def test_few_partial_sums_of_the_angle_error_take_a_small_workgroup(so):
+    fake_hip.run(so, r"""
+a, b, ws, out = (1 << 30), (2 << 30), (3 << 30), (4 << 30)
+for px, threads in ((1, 256), (1024 * 256, 256), (1024 * 256 + 1, 1024), (1 << 22, 1024)):
+    assert L.bn_angle_mse(a, None, b, None, 1, px, ws, out, None) == 0
+    names = [n for n, _ in launches(log())]
+    assert "k_mse_partial" in names[0] and f"k_mse_finalILi{threads}E" in names[1], names
+""")
