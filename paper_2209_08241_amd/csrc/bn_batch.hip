@@ -326,12 +326,15 @@ uint32_t frame_kind(const bn_frame &s, const bn_params *p, bool flat) {
 // 6.1 6.2 6.3 / 5.6 5.7 5.7.  Pair removal: 620 6.7 6.7 6.8 / 6.9 7.1 7.1, 800
 // 7.4 7.5 7.6 / 7.4 7.6 7.7, 1000 8.3 8.4 9.2 / 7.8 7.9 8.3.  Multi-scale, K =
 // 3: 300 5.4 5.6 5.6 / 7.5 7.6 7.3, 800 8.2 8.3 8.5 / 8.7 9.3 9.5, 1000 9.3
-// 9.4 10.0 / 9.2 9.5 10.0).  The lists' kernels carry every tile body, so the
-// lines lie higher than a stack's.
+// 9.4 10.0 / 9.2 9.5 10.0; K = 8, alpha 8, scalar over flat at 1100, 1600 and
+// 2000: 4 frames 0.91 1.08 1.11, 16 frames 0.85 0.96 1.07, 24 frames 0.83 0.97
+// 0.93).  The lists' kernels carry every tile body, so the lines lie higher than
+// a stack's.
 bool list_takes_flat(const bn_params *p, uint64_t pixels) {
     return pixels > (p->method == BN_METHOD_FOUR_PAIR      ? 1u << 19
                      : p->method == BN_METHOD_PAIR_REMOVAL ? 3u << 18
-                                                           : 1u << 20);
+                     : p->scales <= 6                      ? 1u << 20
+                                                           : 1u << 21);
 }
 
 // fill_frame_args' pixels per work item.

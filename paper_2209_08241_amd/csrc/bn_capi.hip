@@ -87,13 +87,15 @@ bool plain_takes_flat(const bn_params *p, uint64_t pixels, bool vec_layout, int3
 // 0.79 0.87 0.91 0.95 1.01 1.04, 2 0.83 0.92 0.97 1.05 1.13 1.17, 16 0.91
 // 1.01 1.08 1.15 1.14 1.24.  Multi-scale, K = 3: 1 0.71 0.74 0.80 0.90 0.95
 // 0.99, 2 0.78 0.80 0.89 1.03 1.07 1.11, 16 0.81 0.92 0.99 1.09 1.00 1.11 (K =
-// 1 and 6 between 0.07 above and 0.10 below).  A single frame's line lies half
-// as high again.  (One frame of 637x479 in multi-scale: 5.1 us scalar, 6.9
-// flat.)
+// 1 and 6 between 0.07 above and 0.10 below; K = 8 at 560 and 820: 2 frames
+// 0.92 0.97, 24 frames 0.96 0.94, with alpha 8 0.87 1.00, 0.80 0.86, all above 1
+// at 1300: twice the line).  A single frame's line lies half as high again.
+// (One frame of 637x479 in multi-scale: 5.1 us scalar, 6.9 flat.)
 bool stack_takes_flat(const bn_params *p, uint32_t n, uint64_t pixels) {
     const uint64_t line = p->method == BN_METHOD_FOUR_PAIR      ? 1u << 18
                           : p->method == BN_METHOD_PAIR_REMOVAL ? 3u << 17
-                                                                : 1u << 19;
+                          : p->scales <= 6                      ? 1u << 19
+                                                                : 1u << 20;
     return pixels > (n == 1 ? line + line / 2 : line);
 }
 

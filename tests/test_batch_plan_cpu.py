@@ -126,7 +126,8 @@ assert launches(log())[0][0] in timed
 
 @pytest.mark.parametrize("method,scales,line", [("four_pair", 0, 1 << 18),
                                                 ("pair_removal", 0, 3 << 17),
-                                                ("multiscale", 3, 1 << 19)])
+                                                ("multiscale", 6, 1 << 19),
+                                                ("multiscale", 7, 1 << 20)])
 def test_small_stacks_of_odd_frames_take_scalar_tiles(so, method, scales, line):
     """Up to `line` pixels in all (half as many again for a single frame)."""
     fake_hip.run(so, f"""
@@ -150,7 +151,8 @@ for frames_, most in ((1, line * 3 // 2), (2, line), (64, line)):
 
 @pytest.mark.parametrize("method,scales,line", [("four_pair", 0, 1 << 19),
                                                 ("pair_removal", 0, 3 << 18),
-                                                ("multiscale", 3, 1 << 20)])
+                                                ("multiscale", 6, 1 << 20),
+                                                ("multiscale", 7, 1 << 21)])
 def test_small_lists_of_odd_frames_take_scalar_tiles(so, method, scales, line):
     """Up to `line` pixels in the whole list: by a plan, for a small list and a
     table, and without one."""
